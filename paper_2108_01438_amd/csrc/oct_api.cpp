@@ -785,9 +785,11 @@ oct_status check_dtcwt(const oct_plan* p, int levels) {
 }
 
 // z = prox(v) with FP64 partials of R(z) in p->partial[0..*np) (for the DT-CWT
-// only when want_value: R(z) then needs a transform of z of its own)
+// only when want_value: R(z) then needs a transform of z of its own); the TV
+// dual goes from p_in to p_out, p_scratch (nullable, may be p_in) is clobbered
 oct_status run_prox(oct_plan* p, int pen, float tau, float bound, int tv_inner, int haar_levels, const float2* v,
-                    float2* z, const float2* p_in, float2* p_out, int* np, hipStream_t s, bool want_value = false) {
+                    float2* z, const float2* p_in, float2* p_out, float2* p_scratch, int* np, hipStream_t s,
+                    bool want_value = false) {
   ProxGeom pg = prox_geom(p);
   if (pen == OCT_PEN_L1) {
     const int nb = 1024;
@@ -803,8 +805,9 @@ oct_status run_prox(oct_plan* p, int pen, float tau, float bound, int tv_inner, 
     if (tv_inner < 1 || tv_inner > 1000) return fail(OCT_E_INVALID, "tv_inner must be 1..1000");
     std::vector<float> mom = fgp_momenta(tv_inner);
     // TV(z) partials only when the value is wanted (the kernels skip it otherwise)
-    HIPCHK(launch_prox_tv(pg, tv_inner, mom.data(), v, z, p_in, p_out, tau, bound,
-                          want_value ? p->partial : nullptr, p->tvwork, s));
+    // X1 is free between the lateral passes: scratch of the volume path
+    HIPCHK(launch_prox_tv(pg, tv_inner, mom.data(), v, z, p_in, p_out, p_scratch, tau, bound,
+                          want_value ? p->partial : nullptr, p->tvwork, p->X1, s));
     *np = want_value ? tv_partials(pg, tv_inner) : 0;
   } else if (pen == OCT_PEN_DTCWT) {
     if (bound < INFINITY) return fail(OCT_E_UNSUPPORTED, "a modulus bound with the DT-CWT step has no closed form");
@@ -1185,12 +1188,16 @@ oct_status oct_prox(oct_plan_t p, int32_t pen, double lambda, double delta, int3
       return OCT_OK;
     }
     const int64_t npel = p->n_img() * (p->lat_dims + 1);
+    // scratch of the volume path: the caller's dual (replaced below in any case),
+    // or p1 unless a resumed solve may still need it
+    float2* scratch = state ? (float2*)state : p->tv_last != p->p1 ? p->p1 : nullptr;
     OCTCHK(run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, (const float2*)state,
-                    p->p0, &np, s));
+                    p->p0, scratch, &np, s));
     if (state) HIPCHK(launch_copy(p->p0, (float2*)state, npel, s));
     return OCT_OK;
   }
-  return run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, nullptr, nullptr, &np, s);
+  return run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, nullptr, nullptr, nullptr,
+                  &np, s);
 }
 
 oct_status oct_dtcwt_filter(int32_t which, float* h0, int32_t* n) {
@@ -1390,7 +1397,7 @@ oct_status oct_mbir_solve(oct_plan_t p, const float* y, const oct_solve_params* 
         double* save = p->partial;
         p->partial = pen_part;
         oct_status st = run_prox(p, prm->penalty, tau, bf, prm->tv_inner, prm->haar_levels, p->xext, zo, pin, pout,
-                                 &npen, s, want_obj);
+                                 pout == p->p0 ? p->p1 : p->p0, &npen, s, want_obj);
         p->partial = save;
         OCTCHK(st);
         if (prm->penalty == OCT_PEN_TV) {
@@ -1462,7 +1469,7 @@ oct_status oct_run_stage(oct_plan_t p, int32_t stage, int32_t pen, const float* 
     case OCT_STAGE_PROX: {
       int np = 0;
       return run_prox(p, pen, 1e-3f, INFINITY, 10, 3, p->xext, p->zb, pen == OCT_PEN_TV ? p->p0 : nullptr,
-                      pen == OCT_PEN_TV ? p->p1 : nullptr, &np, s);
+                      pen == OCT_PEN_TV ? p->p1 : nullptr, p->p0, &np, s);
     }
     default:
       return fail(OCT_E_INVALID, "unknown stage");

@@ -250,9 +250,12 @@ int haar_partials(const ProxGeom& g, int levels);
 hipError_t launch_prox_haar(const ProxGeom& g, int levels, const float2* v, float2* z,
                             float tau, double* partial, hipStream_t s);
 int tv_partials(const ProxGeom& g, int n_inner);
+// p_in (nullable: zero) -> p_out.  Volumes also use z (before it receives the
+// result), img_scratch (one image) and p_scratch (a dual; may be p_in, whose
+// content is then lost; NULL: slower) as scratch.
 hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, const float2* v,
-                          float2* z, const float2* p_in, float2* p_out, float tau, float bound,
-                          double* partial, float2* work, hipStream_t s);
+                          float2* z, const float2* p_in, float2* p_out, float2* p_scratch, float tau,
+                          float bound, double* partial, float2* work, float2* img_scratch, hipStream_t s);
 size_t tv_work_elems(const ProxGeom& g);
 // DT-CWT: z = W^T soft_tau(W v); work holds dtcwt_work_elems complex values
 // (B-scan: four trees and four staging arrays; volume: eight trees and sixteen
@@ -280,4 +283,18 @@ struct Tv2dArgs {
   const float2* pin;        // nullable: cold start
   float2* pout;
   double* partial;
+};
+
+// 3-D TV pass arguments (up to TV3_MAX_T inner steps per pass).
+#define TV3_MAX_T 3
+struct Tv3dArgs {
+  int Nz, Nx, Ny, ntz, ntl, nty, CY;
+  int ntiles;               // ntz * ntl * nty * batch (the launch is padded to a multiple of 8)
+  float tau, step, bound;
+  float m0;                 // momentum of r = p + m0 (p - po)
+  float mom[TV3_MAX_T];
+  const float2* v;
+  int cold;                 // p is zero (what p points at is not used)
+  const float2 *p[3], *po[3];   // the last two duals by component (po NULL: r = p)
+  float2 *out[3], *out_prev[3]; // the last two duals of the pass (out_prev NULL: not stored)
 };

@@ -11,7 +11,7 @@
 //   by the fast gradient projection (FGP) of Beck and Teboulle on the dual,
 //   x = v + tau div p.  The 2-D path runs all inner steps of a tile in LDS
 //   (temporal blocking with a halo as wide as the dependence cone); the
-//   general path (volumes) runs one pass per inner step in global memory.
+//   3-D path runs a few inner steps per pass over memory, walking along y.
 // All partial sums are per block in FP64 and summed in a fixed order.
 #include "oct_fft.h"
 
@@ -320,7 +320,8 @@ hipError_t haar_launch(const ProxGeom& g, const float2* v, float2* z, float tau,
 }
 
 // ---------------------------------------------------------------------------
-// TV by FGP, one pass per inner step (any dimension).
+// TV by FGP, two passes per inner step (B-scans past the tile kernel's inner
+// steps); the divergence and value kernels also serve volumes.
 // strides: depth 1, x Nz, y Nx*Nz.  p, r: [nd][n] complex.
 // ---------------------------------------------------------------------------
 struct TvIdx {
@@ -377,37 +378,234 @@ __global__ void tv_div_kernel(TvIdx d, const float2* __restrict__ v, const float
 }
 
 __global__ void tv_step_kernel(TvIdx d, const float2* __restrict__ dd, float2* r, float2* p, float step, float mom) {
-  const int64_t sx = d.Nz, sy = (int64_t)d.Nx * d.Nz;
+  const int64_t sx = d.Nz;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < d.n; i += (int64_t)gridDim.x * blockDim.x) {
     int iz, ix, iy;
     tv_coords(d, i, iz, ix, iy);
     const float2 c = dd[i];
     float2 gz = (iz < d.Nz - 1) ? csub(dd[i + 1], c) : make_float2(0.f, 0.f);
     float2 gx = (ix < d.Nx - 1) ? csub(dd[i + sx], c) : make_float2(0.f, 0.f);
-    float2 gy = make_float2(0.f, 0.f);
-    if (d.nd == 3 && iy < d.Ny - 1) gy = csub(dd[i + sy], c);
-    float2 pz = r[i], px = r[d.n + i], py = make_float2(0.f, 0.f);
+    float2 pz = r[i], px = r[d.n + i];
     pz = make_float2(pz.x + step * gz.x, pz.y + step * gz.y);
     px = make_float2(px.x + step * gx.x, px.y + step * gx.y);
-    float m2 = pz.x * pz.x + pz.y * pz.y + px.x * px.x + px.y * px.y;
-    if (d.nd == 3) {
-      py = r[2 * d.n + i];
-      py = make_float2(py.x + step * gy.x, py.y + step * gy.y);
-      m2 += py.x * py.x + py.y * py.y;
-    }
+    const float m2 = pz.x * pz.x + pz.y * pz.y + px.x * px.x + px.y * px.y;
     const float sc = m2 > 1.f ? 1.f / sqrtf(m2) : 1.f;
     pz = cscale(pz, sc);
     px = cscale(px, sc);
-    py = cscale(py, sc);
     const float2 oz = p[i], ox = p[d.n + i];
     r[i] = make_float2(pz.x + mom * (pz.x - oz.x), pz.y + mom * (pz.y - oz.y));
     r[d.n + i] = make_float2(px.x + mom * (px.x - ox.x), px.y + mom * (px.y - ox.y));
     p[i] = pz;
     p[d.n + i] = px;
-    if (d.nd == 3) {
-      const float2 oy = p[2 * d.n + i];
-      r[2 * d.n + i] = make_float2(py.x + mom * (py.x - oy.x), py.y + mom * (py.y - oy.y));
-      p[2 * d.n + i] = py;
+  }
+}
+
+// Whole-wave lane shifts (DPP wave_shr:1 / wave_shl:1, zero filled at the
+// wave edge): lane i receives lane i-1 (shr) or lane i+1 (shl).
+__device__ __forceinline__ float lane_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_next(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
+// ---------------------------------------------------------------------------
+// 3-D TV by FGP, T inner steps per pass over memory.  A workgroup owns a
+// 64 x 24 (depth x lateral) column of planes and walks along y; lane = depth
+// sample, each of the 8 waves a strip of TV3_S lateral rows.  Stage t of the
+// walk applies inner step t to the plane t behind the one just loaded, so
+// only the last plane of each stage (r, d, p, v) is held, in registers.
+// Depth neighbours move by lane shifts, strip edges through LDS (one barrier
+// per stage and plane: the primal point's edge is read a plane later).  A
+// step reaches one sample further in every direction: with a halo of T on
+// every side of the tile and of the run of planes, the core is exact.
+//
+// The state is the dual of the last two steps (r = p + mom (p - p_prev) is
+// formed on load), read from one pair of buffers and written to another:
+// the pass reads 7 images (v, p, p_prev) and writes 6, whatever T is, where a
+// step in two kernels (d = v + tau div r stored, then r and p updated) moved
+// 18.  Memory bound (1.0 GB a pass of three steps at 1024 x 96 x 96 in 0.29 ms,
+// with the halos 4.8 TB/s).  A prox of 10 steps: 2998 -> 1296 us there, 45.3 ->
+// 17.1 ms at 2048 x 256 x 256, 176 -> 155 us at 256 x 40 x 45; with runs of at
+// most 2 steps 1446 us, 20.8 ms and 149 us, of one 1744 us, 29.3 ms and 161 us.
+// Three steps of 3 rows per thread fill the registers (242) and, with `hold`,
+// the LDS (150 KB) of a workgroup per CU.
+// ---------------------------------------------------------------------------
+constexpr int TV3_S = 3;
+constexpr int TV3_WAVES = 8;
+constexpr int TV3_ROWS = TV3_S * TV3_WAVES;
+
+// v or zero, by value (a conditional on two array elements would select between their addresses)
+__device__ __forceinline__ float2 keep_if(bool c, float2 v) { return make_float2(c ? v.x : 0.f, c ? v.y : 0.f); }
+
+// FIRST: one dual on entry (r = p; p itself zero when a.cold)
+template <int T, bool FIRST>
+__global__ void __launch_bounds__(TV3_WAVES * 64) tv3d_march_kernel(Tv3dArgs a) {
+  __shared__ float2 xr[T][2][TV3_WAVES + 1][64];   // last r_x row of wave w in [w + 1]; [0] stays zero
+  __shared__ float2 xd[T][2][TV3_WAVES + 1][64];   // first d row of wave w in [w]; [TV3_WAVES] stays zero
+  // p and v of the plane a stage holds, each slot its own thread's (no barrier): too many for registers
+  constexpr int HS = T > 1 ? T - 1 : 1;
+  __shared__ float2 hold[HS][4][T > 1 ? TV3_S : 1][TV3_WAVES * 64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // consecutive tiles (depth, then lateral neighbours) on one XCD: their halos meet in its L2
+  const int per = gridDim.x >> 3;
+  const int bid = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if (bid >= a.ntiles) return;
+  const int tz = bid % a.ntz;
+  int q = bid / a.ntz;
+  const int tl = q % a.ntl;
+  q /= a.ntl;
+  const int ty = q % a.nty;
+  const int b = q / a.nty;
+  const int Nz = a.Nz, Nx = a.Nx, Ny = a.Ny;
+  const int CZ = 64 - 2 * T, CL = TV3_ROWS - 2 * T;
+  const int n = tz * CZ - T + lane;
+  const int l0 = tl * CL - T + w * TV3_S;
+  const int y0 = ty * a.CY, y1 = min(y0 + a.CY, Ny);
+  const bool nin = n >= 0 && n < Nz;
+  const bool zedge = n >= 0 && n < Nz - 1;                    // has a forward depth neighbour
+  const bool zcore = nin && lane >= T && lane < 64 - T;
+  const float tau = a.tau, step = a.step, bound = a.bound;
+  for (int i = threadIdx.x; i < T * 2 * 64; i += TV3_WAVES * 64) {
+    xr[i >> 7][(i >> 6) & 1][0][i & 63] = make_float2(0.f, 0.f);
+    xd[i >> 7][(i >> 6) & 1][TV3_WAVES][i & 63] = make_float2(0.f, 0.f);
+  }
+  // byte offsets of the thread's samples inside a plane (clamped: loads of samples outside are masked)
+  uint32_t off[TV3_S];
+#pragma unroll
+  for (int s = 0; s < TV3_S; ++s)
+    off[s] = ((uint32_t)min(max(l0 + s, 0), Nx - 1) * (uint32_t)Nz + (uint32_t)min(max(n, 0), Nz - 1)) * 8u;
+  auto at = [](const float2* plane, uint32_t o) __attribute__((always_inline)) {
+    return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(plane) + o);
+  };
+  const int64_t plane = (int64_t)Nx * Nz;
+  auto plane_off = [&](int y) __attribute__((always_inline)) { return ((int64_t)b * Ny + y) * plane; };
+
+  // plane being loaded: v, p and p_prev (samples outside the image: a clamped
+  // one's values, replaced by zero on use)
+  float2 lv[TV3_S], lp[3][TV3_S], lo[FIRST ? 1 : 3][TV3_S];
+  auto load_plane = [&](int y) __attribute__((always_inline)) {
+    const int64_t po = plane_off(min(max(y, 0), Ny - 1));
+#pragma unroll
+    for (int s = 0; s < TV3_S; ++s) {
+      lv[s] = at(a.v + po, off[s]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        lp[c][s] = at(a.p[c] + po, off[s]);
+        if constexpr (!FIRST) lo[c][s] = at(a.po[c] + po, off[s]);
+      }
+    }
+  };
+
+  // per stage, the previous plane's r and d (and in `hold` its p and v)
+  float2 cr[T][3][TV3_S], cd[T][TV3_S];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int s = 0; s < TV3_S; ++s) {
+      cd[t][s] = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cr[t][c][s] = make_float2(0.f, 0.f);
+      if (t < T - 1)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) hold[t][c][s][threadIdx.x] = make_float2(0.f, 0.f);
+    }
+
+  load_plane(y0 - T);
+  int par = 0;
+  for (int Y = y0 - T; Y < y1 + T; ++Y, par ^= 1) {
+    float2 rn[3][TV3_S], pn[3][TV3_S], vn[TV3_S];
+    const bool yin = Y >= 0 && Y < Ny;
+#pragma unroll
+    for (int s = 0; s < TV3_S; ++s) {
+      const bool in = nin && yin && l0 + s >= 0 && l0 + s < Nx;
+      vn[s] = keep_if(in, lv[s]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        pn[c][s] = keep_if(FIRST ? in && !a.cold : in, lp[c][s]);
+        rn[c][s] = pn[c][s];
+        if constexpr (!FIRST) {
+          const float2 o = keep_if(in, lo[c][s]);
+          rn[c][s] = make_float2(pn[c][s].x + a.m0 * (pn[c][s].x - o.x), pn[c][s].y + a.m0 * (pn[c][s].y - o.y));
+        }
+      }
+    }
+    if (Y + 1 < y1 + T) load_plane(Y + 1);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      // incoming: r_t, p_t, v of plane yt; held: r_t, d_t, p_t, v of plane yt - 1
+      const int yt = Y - t;
+      const bool ye = yt >= 0 && yt < Ny - 1, yem = yt - 1 >= 0 && yt - 1 < Ny - 1;   // forward y edges
+      auto rx_in = [&](int s) __attribute__((always_inline)) {   // r_x where it has an edge
+        const int l = l0 + s;
+        return keep_if(l >= 0 && l < Nx - 1, rn[1][s]);
+      };
+      xr[t][par][w + 1][lane] = rx_in(TV3_S - 1);
+      __syncthreads();
+      float2 d[TV3_S];
+#pragma unroll
+      for (int s = 0; s < TV3_S; ++s) {
+        const float2 rz = keep_if(zedge, rn[0][s]);
+        const float2 rx = rx_in(s);
+        float2 rxp;
+        if (s > 0) rxp = rx_in(s - 1);
+        else rxp = xr[t][par][w][lane];
+        const float2 ry = keep_if(ye, rn[2][s]), ryp = keep_if(yem, cr[t][2][s]);
+        const float dx = rz.x - lane_prev(rz.x) + rx.x - rxp.x + ry.x - ryp.x;
+        const float dy = rz.y - lane_prev(rz.y) + rx.y - rxp.y + ry.y - ryp.y;
+        float2 x = make_float2(fmaf(tau, dx, vn[s].x), fmaf(tau, dy, vn[s].y));
+        const float m2 = x.x * x.x + x.y * x.y;
+        if (m2 > bound * bound) x = cscale(x, bound * rsqrtf(m2));
+        d[s] = x;
+      }
+      xd[t][par][w][lane] = d[0];   // read with the next plane
+      // the held plane's step; the last two steps' duals leave for memory: plane
+      // Y - T of the last, Y - T + 1 of the one before
+      const int yo = yt - 1;
+      float2* const* out = t == T - 1 ? a.out : a.out_prev;
+      const bool store = t >= T - 2 && out[0] && yo >= y0 && yo < y1;
+      const int64_t po = plane_off(yo);
+#pragma unroll
+      for (int s = 0; s < TV3_S; ++s) {
+        const int l = l0 + s;
+        const float2 c = cd[t][s];
+        float2 dl;
+        if (s < TV3_S - 1) dl = cd[t][s + 1];
+        else dl = xd[t][par ^ 1][w + 1][lane];
+        const float2 nz = make_float2(lane_next(c.x), lane_next(c.y));
+        const float2 gz = keep_if(zedge, csub(nz, c)), gx = keep_if(l >= 0 && l < Nx - 1, csub(dl, c)),
+                     gy = keep_if(yem, csub(d[s], c));
+        float2 p1[3];
+        p1[0] = make_float2(fmaf(step, gz.x, cr[t][0][s].x), fmaf(step, gz.y, cr[t][0][s].y));
+        p1[1] = make_float2(fmaf(step, gx.x, cr[t][1][s].x), fmaf(step, gx.y, cr[t][1][s].y));
+        p1[2] = make_float2(fmaf(step, gy.x, cr[t][2][s].x), fmaf(step, gy.y, cr[t][2][s].y));
+        const float m2 = p1[0].x * p1[0].x + p1[0].y * p1[0].y + p1[1].x * p1[1].x + p1[1].y * p1[1].y +
+                         (p1[2].x * p1[2].x + p1[2].y * p1[2].y);
+        const float sc = m2 > 1.f ? __builtin_amdgcn_rsqf(m2) : 1.f;
+        const int row = w * TV3_S + s;
+        const bool st = store && zcore && row >= T && row < TV3_ROWS - T && l < Nx;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          p1[k] = cscale(p1[k], sc);
+          if (t >= T - 2 && st)
+            *reinterpret_cast<float2*>(reinterpret_cast<char*>(out[k] + po) + off[s]) = p1[k];
+          // hold the incoming plane; the next stage takes the finished one
+          cr[t][k][s] = rn[k][s];
+          if (t < T - 1) {
+            const float2 ph = hold[t][k][s][threadIdx.x];
+            hold[t][k][s][threadIdx.x] = pn[k][s];
+            rn[k][s] = make_float2(p1[k].x + a.mom[t] * (p1[k].x - ph.x), p1[k].y + a.mom[t] * (p1[k].y - ph.y));
+            pn[k][s] = p1[k];
+          }
+        }
+        if (t < T - 1) {
+          const float2 vh = hold[t][3][s][threadIdx.x];
+          hold[t][3][s][threadIdx.x] = vn[s];
+          vn[s] = vh;
+        }
+        cd[t][s] = d[s];
+        __builtin_amdgcn_sched_barrier(0);   // one row at a time: interleaved rows would not fit the registers
+      }
     }
   }
 }
@@ -442,15 +640,6 @@ __global__ void tv_value_kernel(TvIdx d, const float2* __restrict__ z, double* p
 // ---------------------------------------------------------------------------
 constexpr int TV_S = 8;
 constexpr int TV_WAVES = 16;
-
-// Whole-wave lane shifts (DPP wave_shr:1 / wave_shl:1, zero filled at the
-// wave edge): lane i receives lane i-1 (shr) or lane i+1 (shl).
-__device__ __forceinline__ float lane_prev(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_next(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
-}
 
 // The dual is kept zero wherever its component has no forward edge (last
 // index along that axis, and every sample outside the image).  The step of
@@ -729,11 +918,122 @@ int tv_partials(const ProxGeom& g, int n_inner) {
   return grid_for(n, 256);
 }
 
+// Planes along y per workgroup: the pass takes rounds of workgroups over the
+// 256 CUs (one resident per CU), each CY planes and 2 T of halo long.
+static hipError_t tv3d_pass(const ProxGeom& g, int T, const float2* v, float2* const* p, float2* const* po, float m0,
+                            const float* mom, float2* const* out, float2* const* out_prev, float tau, float bound,
+                            hipStream_t s) {
+  Tv3dArgs a{};
+  a.Nz = g.Nz;
+  a.Nx = g.Nx;
+  a.Ny = g.Ny;
+  const int CZ = 64 - 2 * T, CL = TV3_ROWS - 2 * T;
+  a.ntz = (g.Nz + CZ - 1) / CZ;
+  a.ntl = (g.Nx + CL - 1) / CL;
+  const int64_t cols = (int64_t)a.ntz * a.ntl * g.B;
+  int64_t best = INT64_MAX;
+  for (int n = 1; n <= g.Ny; ++n) {
+    const int cy = (g.Ny + n - 1) / n, nty = (g.Ny + cy - 1) / cy;
+    const int64_t cost = ((cols * nty + 255) / 256) * (cy + 2 * T + 2);
+    if (cost < best) {
+      best = cost;
+      a.CY = cy;
+      a.nty = nty;
+    }
+  }
+  const int64_t tiles = cols * a.nty;
+  if (tiles > (int64_t)1 << 30) return hipErrorInvalidConfiguration;
+  a.ntiles = (int)tiles;
+  a.tau = tau;
+  a.step = 1.0f / (12.0f * tau);
+  a.bound = bound;
+  a.m0 = m0;
+  for (int t = 0; t < T; ++t) a.mom[t] = mom[t];
+  a.v = v;
+  a.cold = p[0] == nullptr;
+  for (int c = 0; c < 3; ++c) {
+    a.p[c] = a.cold ? v : p[c];   // a cold start loads (and ignores) something readable
+    a.po[c] = po[c];
+    a.out[c] = out[c];
+    a.out_prev[c] = T > 1 ? out_prev[c] : nullptr;
+  }
+  const dim3 nb((a.ntiles + 7) & ~7), nt(TV3_WAVES * 64);
+  const bool first = po[0] == nullptr;
+  switch (T) {
+    case 1:
+      if (first) hipLaunchKernelGGL((tv3d_march_kernel<1, true>), nb, nt, 0, s, a);
+      else hipLaunchKernelGGL((tv3d_march_kernel<1, false>), nb, nt, 0, s, a);
+      break;
+    case 2:
+      if (first) hipLaunchKernelGGL((tv3d_march_kernel<2, true>), nb, nt, 0, s, a);
+      else hipLaunchKernelGGL((tv3d_march_kernel<2, false>), nb, nt, 0, s, a);
+      break;
+    case 3:
+      if (first) hipLaunchKernelGGL((tv3d_march_kernel<3, true>), nb, nt, 0, s, a);
+      else hipLaunchKernelGGL((tv3d_march_kernel<3, false>), nb, nt, 0, s, a);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// Inner steps of the 3-D path.  Runs of T steps (3 and 2) alternate between two
+// pairs of duals, {last, previous} each: one pair holds p_out, the other is
+// made of the scratch (work: four images, z and img_scratch: one each, z being
+// written only after the steps; and p_scratch, three, which may be p_in: it is
+// read by the first pass only).  Without p_scratch: one step at a time over
+// three duals.
+static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, const float2* v, float2* z,
+                             const float2* p_in, float2* p_out, float2* p_scratch, float tau, float bound,
+                             float2* work, float2* img_scratch, hipStream_t s) {
+  struct Dual {
+    float2* c[3];
+  };
+  const int64_t n = (int64_t)g.B * g.Ny * g.Nx * g.Nz;
+  auto packed = [&](const float2* p) {
+    float2* q = const_cast<float2*>(p);
+    return q ? Dual{{q, q + n, q + 2 * n}} : Dual{{nullptr, nullptr, nullptr}};
+  };
+  const Dual in = packed(p_in), out = packed(p_out), s1 = packed(work), s2{{work + 3 * n, z, img_scratch}},
+             none = packed(nullptr);
+  const int maxT = p_scratch ? TV3_MAX_T : 1;
+  const int passes = (n_inner + maxT - 1) / maxT;   // of at most maxT steps, as even as possible
+  Dual last = in, prev = none;
+  int k = 0;
+  for (int i = 0; i < passes; ++i) {
+    const int T = (n_inner - k + (passes - i) - 1) / (passes - i);
+    const int left = passes - 1 - i;
+    Dual o, op = none;   // where this pass leaves its last two duals
+    if (maxT == 1) {
+      o = left % 3 == 0 ? out : left % 3 == 1 ? s1 : s2;
+    } else {
+      // the pair with p_out when an even number of passes is left; the other
+      // duals of the pairs: p_scratch is not written by the first pass
+      const bool outer = left % 2 == 0;
+      const bool scratch_with_out = passes % 2 == 0;
+      if (outer) {
+        o = out;
+        op = scratch_with_out ? packed(p_scratch) : s1;
+      } else {
+        o = s2;
+        op = scratch_with_out ? s1 : packed(p_scratch);
+      }
+      if (left == 0) op = none;   // nothing follows the last pass
+    }
+    const hipError_t e = tv3d_pass(g, T, v, last.c, prev.c, k > 0 ? mom[k - 1] : 0.f, mom + k, o.c, op.c, tau, bound, s);
+    if (e != hipSuccess) return e;
+    prev = maxT == 1 ? last : op;
+    last = o;
+    k += T;
+  }
+  return hipSuccess;
+}
+
 // p_in (nullable = zero) -> p_out; z = v + tau div p_out; partial (nullable:
 // not computed) = TV(z).
 hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, const float2* v, float2* z,
-                          const float2* p_in, float2* p_out, float tau, float bound, double* partial,
-                          float2* work, hipStream_t s) {
+                          const float2* p_in, float2* p_out, float2* p_scratch, float tau, float bound,
+                          double* partial, float2* work, float2* img_scratch, hipStream_t s) {
   if (tv_tiled(g, n_inner)) {
     Tv2dArgs a{};
     a.Nz = g.Nz;
@@ -772,19 +1072,24 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
   // for B-scans Ny = 1 and the x index never crosses a batch boundary because
   // coordinates are taken modulo each axis length.
   const int64_t np = d.n * d.nd;
-  float2* dd = work;
-  float2* r = work + d.n;
   const int gb = grid_for(d.n, 256);
-  if (p_in) {
-    hipLaunchKernelGGL(copy_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_in, p_out, np);
+  if (g.lateral_dims == 1) {   // inner steps past the tile kernel's halo: two passes per step
+    float2* dd = work;
+    float2* r = work + d.n;
+    if (p_in) {
+      hipLaunchKernelGGL(copy_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_in, p_out, np);
+    } else {
+      hipLaunchKernelGGL(zero_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_out, np);
+    }
+    hipLaunchKernelGGL(copy_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_out, r, np);
+    const float step = 1.0f / (4.0f * d.nd * tau);
+    for (int k = 0; k < n_inner; ++k) {
+      hipLaunchKernelGGL(tv_div_kernel, dim3(gb), dim3(256), 0, s, d, v, r, tau, bound, dd);
+      hipLaunchKernelGGL(tv_step_kernel, dim3(gb), dim3(256), 0, s, d, dd, r, p_out, step, mom[k]);
+    }
   } else {
-    hipLaunchKernelGGL(zero_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_out, np);
-  }
-  hipLaunchKernelGGL(copy_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, p_out, r, np);
-  const float step = 1.0f / (4.0f * d.nd * tau);
-  for (int k = 0; k < n_inner; ++k) {
-    hipLaunchKernelGGL(tv_div_kernel, dim3(gb), dim3(256), 0, s, d, v, r, tau, bound, dd);
-    hipLaunchKernelGGL(tv_step_kernel, dim3(gb), dim3(256), 0, s, d, dd, r, p_out, step, mom[k]);
+    const hipError_t e = tv3d_steps(g, n_inner, mom, v, z, p_in, p_out, p_scratch, tau, bound, work, img_scratch, s);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(tv_div_kernel, dim3(gb), dim3(256), 0, s, d, v, p_out, tau, bound, z);
   if (partial) hipLaunchKernelGGL(tv_value_kernel, dim3(gb), dim3(256), 0, s, d, z, partial);
