@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liboct.so")
-SOURCES = ["oct_lateral.hip", "oct_nufft.hip", "oct_prox.hip", "oct_direct.hip", "oct_literal.hip", "oct_dtcwt.hip", "oct_api.cpp"]
+SOURCES = ["oct_lateral.hip", "oct_nufft.hip", "oct_column.hip", "oct_prox.hip", "oct_direct.hip", "oct_literal.hip", "oct_dtcwt.hip", "oct_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed FP32 instructions are disabled: plain float code is compiled to
@@ -37,7 +37,7 @@ def _compile(src: str) -> str:
 
 def build_library(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs

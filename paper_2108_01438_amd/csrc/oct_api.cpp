@@ -186,6 +186,12 @@ struct oct_plan {
   int64_t X1s = 0;               // column stride of X1's y rows (n_x, or n_x + 1 for a volume)
   int4* pairs = nullptr;
   int n_pairs = 0;
+  // column pairs on the twice oversampled grid (oct_column.hip)
+  bool col = false;
+  ColPlan colf{}, coli{};
+  float2 *twC = nullptr, *deap_odd = nullptr;   // deap_odd and spans: parts of twC's allocation
+  ColSpan* spans = nullptr;
+  int col_span = 0;
   // every measurement pixel observed (no mask, or a mask of all ones): on the
   // half-spectrum path the residual seam reduces to R^ = W_h / N_lat - Y_h
   bool full = true;
@@ -437,6 +443,21 @@ NufftArgs nufft_args(const oct_plan* p) {
   return a;
 }
 
+ColArgs col_args(const oct_plan* p) {
+  ColArgs a{};
+  a.n = nufft_args(p);
+  a.f = p->colf;
+  a.i = p->coli;
+  a.tw = p->twC;
+  a.deap_odd = p->deap_odd;
+  a.spans = p->spans;
+  a.inv_ct = 1.0 / p->ct;
+  a.inv_dk = 1.0 / p->dk;
+  a.rs = col_row_cells((int)p->Nz);
+  a.span = p->col_span;
+  return a;
+}
+
 hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 // NUFFT column arguments of the literal chain's K: the N even detector
@@ -453,7 +474,8 @@ NufftArgs even_args(const oct_plan* p) {
 // X1 (lateral spectra of the image) -> W (spectra at the detector pixels)
 oct_status run_cols_fwd(oct_plan* p, hipStream_t s, bool half) {
   if (half) {
-    HIPCHK(launch_nufft_fwd_pair(nufft_args(p), p->X1, p->W, s));
+    if (p->col) HIPCHK(launch_col_fwd(col_args(p), p->X1, p->W, s));
+    else HIPCHK(launch_nufft_fwd_pair(nufft_args(p), p->X1, p->W, s));
     return OCT_OK;
   }
   if (p->model == OCT_MODEL_DIRECT) {
@@ -469,7 +491,8 @@ oct_status run_cols_fwd(oct_plan* p, hipStream_t s, bool half) {
 // W -> X1 (the exact adjoint of run_cols_fwd)
 oct_status run_cols_adj(oct_plan* p, hipStream_t s, bool half) {
   if (half) {
-    HIPCHK(launch_nufft_adj_pair(nufft_args(p), p->W, p->X1, s));
+    if (p->col) HIPCHK(launch_col_adj(col_args(p), p->W, p->X1, s));
+    else HIPCHK(launch_nufft_adj_pair(nufft_args(p), p->W, p->X1, s));
     return OCT_OK;
   }
   if (p->model == OCT_MODEL_DIRECT) {
@@ -652,6 +675,11 @@ oct_status run_cols_fwd_res(oct_plan* p, const float2* yh, double* partial, int*
 // fits it (R^ stays in registers), else the residual-writing forward kernel
 // and the adjoint kernel over W
 oct_status run_cols_normal(oct_plan* p, const float2* yh, double* partial, int* nparts, hipStream_t s) {
+  if (p->col) {
+    HIPCHK(launch_col_normal(col_args(p), p->X1, yh, partial, p->X1, s));
+    if (nparts) *nparts = (int)(p->n_pairs * p->B);
+    return OCT_OK;
+  }
   const NufftArgs a = nufft_args(p);
   if (nufft_normal_pair_supported(a)) {
     HIPCHK(launch_nufft_normal_pair(a, p->X1, yh, partial, p->X1, s));
@@ -845,6 +873,7 @@ size_t oct_plan_footprint_bytes(const oct_geometry* g, int32_t penalty) {
        (size_t)Nlat * (8 + 4) * 2 + (size_t)g->n_k * 8 + (size_t)Nlat * ((g->n_k + 31) / 32) * 4;
   b += (size_t)x1_elems(*g) * 8 + (size_t)w_elems(*g) * 8;  // workspace X1, W
   b += (size_t)Nlat * 16;                        // column-pair table of the half-spectrum path
+  b += (size_t)Nlat * sizeof(ColSpan) + (size_t)g->n_depth * 48;   // its spans and transform tables at K = 2 N
   b += (size_t)M * 4;                            // measurements scaled per item (per-item weights)
   b += (size_t)w_elems(*g) * 8;                  // lateral spectrum of y (solves of a fully observed plan)
   if (g->model == OCT_MODEL_LITERAL)             // K's samples and the literal chain's tables
@@ -1018,7 +1047,45 @@ oct_status oct_plan_create(const oct_geometry* g, const uint8_t* mask, oct_plan_
     }
     p->n_pairs = (int)pr.size();
     if ((st = upload(p, &p->pairs, pr)) != OCT_OK) return cleanup(st);
-    p->hs = nufft_pair_supported(nufft_args(p));
+    std::vector<float2> twc;
+    std::vector<ColSpan> sps;
+    if (col_plan((int)p->Nz, &p->colf, &p->coli, &twc)) {
+      sps.resize(pr.size());
+      for (size_t i = 0; i < pr.size(); ++i) {
+        const int4 e = pr[i];
+        ColSpan& c = sps[i];
+        c.x0 = (int)((e.x / p->Nx) * p->X1s + e.x % p->Nx);
+        c.x1 = (int)((e.y / p->Nx) * p->X1s + e.y % p->Nx);
+        c.q2 = q2[e.x];
+        c.beam = beam[e.x];
+        // base cells (floor of t, shifted by up to 1.3e-4: see oct_column.hip), with a margin for rounding
+        const double a0 = k2x4[0] - c.q2, a1 = k2x4[p->Mk - 1] - c.q2;
+        c.evan = !(a0 > 1e-9 * k2x4[0]);
+        c.umin = a0 > 0 ? (int)std::floor(p->ct * std::sqrt(a0) - 1e-6) : 0;
+        c.umax = a1 > 0 ? (int)std::floor(p->ct * std::sqrt(a1) + 1.5e-4) : -1;
+        c.umin = std::max(c.umin, 0);
+        c.cell0 = (int)((((int64_t)c.umin - p->J / 2 + 1) % p->K + p->K) % p->K);
+        p->col_span = std::max(p->col_span, c.umax - c.umin + 1);
+      }
+      p->col = col_supported(col_args(p));
+    }
+    if (p->col) {
+      const size_t nt = twc.size();
+      for (int64_t n = 0; n < p->Nz; ++n) {
+        const double a = -kPi * (double)(n - p->nc) / (double)p->Nz;
+        const double d = 1.0 / kb0_ft((double)(n - p->nc) / (double)p->K, p->J, p->kbb);
+        twc.push_back(make_float2((float)(d * std::cos(a)), (float)(d * std::sin(a))));
+      }
+      // one upload: twiddle rows (16-byte rows first), deap_odd, spans
+      twc.resize((twc.size() + 1) & ~(size_t)1);
+      const size_t ns = twc.size();
+      twc.resize(ns + (sps.size() * sizeof(ColSpan) + sizeof(float2) - 1) / sizeof(float2));
+      std::memcpy(static_cast<void*>(twc.data() + ns), sps.data(), sps.size() * sizeof(ColSpan));
+      if ((st = upload(p, &p->twC, twc)) != OCT_OK) return cleanup(st);
+      p->deap_odd = p->twC + nt;
+      p->spans = reinterpret_cast<ColSpan*>(p->twC + ns);
+    }
+    p->hs = p->col || nufft_pair_supported(nufft_args(p));
   }
   if ((st = dev_alloc(p, &p->X1, x1_elems(p->g))) != OCT_OK) return cleanup(st);
   if ((st = dev_alloc(p, &p->W, w_elems(p->g))) != OCT_OK) return cleanup(st);
@@ -1151,7 +1218,7 @@ oct_status oct_grad(oct_plan_t p, const void* x, const float* y, void* gout, dou
   // takes three passes (y, x, y), and where the one-kernel column pair saves
   // the spectrum's round trip; a B-scan whose pairs need the two kernels
   // keeps its single seam pass.
-  if (spectral_seam(p, false) && (p->lat_dims == 2 || nufft_normal_pair_supported(nufft_args(p)))) {
+  if (spectral_seam(p, false) && (p->lat_dims == 2 || p->col || nufft_normal_pair_supported(nufft_args(p)))) {
     OCTCHK(run_meas_adjoint(p, y, s, true));   // W = Y_h, read by the column kernels
     OCTCHK(run_lat_forward(p, (const float2*)x, nullptr, nullptr, 0.f, s));
     OCTCHK(run_cols_normal(p, p->W, half_resid_sq ? p->partial : nullptr, &np, s));

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #define OCT_MAX_STAGES 16
 #define OCT_KB_DEG 7             // degree of each KB polynomial piece
 #define OCT_MAX_J 8
@@ -163,6 +165,32 @@ struct PairRes {
   double nlat;
 };
 
+// Column pairs on a grid oversampled exactly twice (oct_column.hip): stages of
+// an N-point transform (radices up to 16, twiddle rows as FftDesc's).
+struct ColPlan {
+  int ns;
+  int radix[4], sub[4], tw_off[4];   // sub: product of the radices before each stage
+  FastDiv div_sub[4];
+};
+// A pair's columns (offsets within a batch item) and base cells: umin is the
+// first sample's base cell or one before it (0 with evanescent samples), umax
+// the last one's or one after it, cell0 the grid cell of umin's first tap.
+struct ColSpan {
+  int x0, x1, umin, umax, cell0, evan;
+  float beam;
+  double q2;
+};
+struct ColArgs {
+  NufftArgs n;
+  const ColSpan* spans;    // [n_pairs]
+  ColPlan f, i;            // forward stages (smallest radix first) and inverse ones (the reverse)
+  const float2* tw;        // twiddle rows of both
+  const float2* deap_odd;  // [Nz] deap e^{-i pi (n - n_c) / N}
+  double inv_ct, inv_dk;
+  int rs;                  // cells of an LDS row
+  int span;                // largest number of base cells of a column
+};
+
 // Launchers (kernels in the .hip files; all asynchronous on `s`).
 hipError_t launch_lateral(LatMode mode, const LatArgs& a, hipStream_t s);
 int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* nthr, int* rowstride);
@@ -189,6 +217,17 @@ hipError_t launch_nufft_normal_pair(const NufftArgs& a, const float2* X1, const 
 size_t nufft_normal_pair_lds_bytes(const NufftArgs& a);
 bool nufft_normal_pair_supported(const NufftArgs& a);
 bool nufft_pair_supported(const NufftArgs& a);   // LDS and thread limits of the pair kernels
+// The same column pairs where K = 2 N (col_supported): forward, adjoint, and
+// both around the residual spectrum of a fully observed plan.
+bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw);
+bool col_supported(const ColArgs& a);
+int col_threads(const ColArgs& a, int* spt, int* mb);
+int col_row_cells(int N);
+size_t col_lds_bytes(int N);
+hipError_t launch_col_fwd(const ColArgs& a, const float2* X1, float2* Wh, hipStream_t s);
+hipError_t launch_col_adj(const ColArgs& a, const float2* Rh, float2* X, hipStream_t s);
+hipError_t launch_col_normal(const ColArgs& a, const float2* X1, const float2* yh, double* partial, float2* X,
+                             hipStream_t s);
 
 // Reductions and elementwise helpers.
 hipError_t launch_reduce_sum(const double* partial, int n, double* out, double scale,

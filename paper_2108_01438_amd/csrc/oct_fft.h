@@ -201,6 +201,103 @@ template <bool INV> struct Dft<3, INV> : DftOdd<3, INV> {};
 template <bool INV> struct Dft<5, INV> : DftOdd<5, INV> {};
 template <bool INV> struct Dft<7, INV> : DftOdd<7, INV> {};
 
+// Radix R1 R2, R1 and R2 coprime, by the prime-factor map (no twiddles between
+// the factors): input n = R2 n1 + R1 n2, output k = k1 mod R1 = k2 mod R2.
+template <int R1, int R2>
+constexpr int pfa_out(int k1, int k2) {
+  for (int k = 0; k < R1 * R2; ++k)
+    if (k % R1 == k1 && k % R2 == k2) return k;
+  return 0;
+}
+template <int R1, int R2, bool INV> struct DftPfa {
+  static __device__ __forceinline__ void run(float2* a) {
+    constexpr int R = R1 * R2;
+    float2 t[R1][R2];
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) {
+#pragma unroll
+      for (int n2 = 0; n2 < R2; ++n2) t[n1][n2] = a[(R2 * n1 + R1 * n2) % R];
+      Dft<R2, INV>::run(t[n1]);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) {
+      float2 c[R1];
+#pragma unroll
+      for (int n1 = 0; n1 < R1; ++n1) c[n1] = t[n1][k2];
+      Dft<R1, INV>::run(c);
+#pragma unroll
+      for (int k1 = 0; k1 < R1; ++k1) a[pfa_out<R1, R2>(k1, k2)] = c[k1];
+    }
+  }
+};
+template <bool INV> struct Dft<6, INV> : DftPfa<2, 3, INV> {};
+template <bool INV> struct Dft<10, INV> : DftPfa<2, 5, INV> {};
+template <bool INV> struct Dft<12, INV> : DftPfa<4, 3, INV> {};
+template <bool INV> struct Dft<14, INV> : DftPfa<2, 7, INV> {};
+template <bool INV> struct Dft<15, INV> : DftPfa<3, 5, INV> {};
+
+// Radix 9 and 16 as 3 x 3 and 4 x 4: n = Q n1 + n2, k = k1 + Q k2, with the
+// factors w^{n2 k1}, w = e^{-+ 2 pi i / R}, as constants.
+template <int R> struct SquareRoots;   // cos and sin of 2 pi k / R
+template <> struct SquareRoots<9> {
+  static __device__ __forceinline__ float c(int k) {
+    const float v[5] = {1.0f, 0.76604444311897803520f, 0.17364817766693034885f, -0.5f, -0.93969262078590838405f};
+    return v[k];
+  }
+  static __device__ __forceinline__ float s(int k) {
+    const float v[5] = {0.0f, 0.64278760968653932632f, 0.98480775301220805937f, 0.86602540378443864676f,
+                        0.34202014332566873304f};
+    return v[k];
+  }
+};
+template <> struct SquareRoots<16> {
+  static __device__ __forceinline__ float c(int k) {
+    const float v[10] = {1.0f, 0.92387953251128675613f, 0.70710678118654752440f, 0.38268343236508977173f, 0.0f,
+                         -0.38268343236508977173f, -0.70710678118654752440f, -0.92387953251128675613f, -1.0f,
+                         -0.92387953251128675613f};
+    return v[k];
+  }
+  static __device__ __forceinline__ float s(int k) {
+    const float v[10] = {0.0f, 0.38268343236508977173f, 0.70710678118654752440f, 0.92387953251128675613f, 1.0f,
+                         0.92387953251128675613f, 0.70710678118654752440f, 0.38268343236508977173f, 0.0f,
+                         -0.38268343236508977173f};
+    return v[k];
+  }
+};
+template <int Q, bool INV> struct DftSquare {
+  static __device__ __forceinline__ void run(float2* a) {
+    float2 t[Q][Q];
+#pragma unroll
+    for (int n2 = 0; n2 < Q; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < Q; ++n1) t[n2][n1] = a[Q * n1 + n2];
+      Dft<Q, INV>::run(t[n2]);
+#pragma unroll
+      for (int k1 = 1; k1 < Q; ++k1) {
+        if (n2 == 0) continue;
+        const int m = n2 * k1;
+        if (Q == 4 && m == 4) {
+          t[n2][k1] = rot90<INV>(t[n2][k1]);
+        } else {
+          const float wc = SquareRoots<Q * Q>::c(m), ws = INV ? SquareRoots<Q * Q>::s(m) : -SquareRoots<Q * Q>::s(m);
+          t[n2][k1] = cmul(t[n2][k1], make_float2(wc, ws));
+        }
+      }
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < Q; ++k1) {
+      float2 c[Q];
+#pragma unroll
+      for (int n2 = 0; n2 < Q; ++n2) c[n2] = t[n2][k1];
+      Dft<Q, INV>::run(c);
+#pragma unroll
+      for (int k2 = 0; k2 < Q; ++k2) a[k1 + Q * k2] = c[k2];
+    }
+  }
+};
+template <bool INV> struct Dft<9, INV> : DftSquare<3, INV> {};
+template <bool INV> struct Dft<16, INV> : DftSquare<4, INV> {};
+
 // One Stockham stage over `nrows` transforms of length n stored at
 // buf[row * rowstride + i]; tw: this stage's twiddle rows (global memory).
 template <int R, int MAXB, bool INV>
