@@ -40,50 +40,55 @@ __global__ void meas_to_complex_kernel(const float* __restrict__ y, const uint32
 }
 
 // One block per A-scan: for every spectral pixel the last observed pixel at
-// or before it and the first at or after it (two-level scans over per-thread
-// chunks of at most 32 pixels: Mk <= 8192), then linear interpolation between
+// or before it and the first at or after it, then linear interpolation between
 // them; the nearest observed value outside the observed range; zero when
-// nothing is observed.
-constexpr int INTERP_MAX_MK = 8192;
+// nothing is observed.  Thread t < words owns mask word t (Mk <= 8192: at most
+// one per thread); a scan over the words gives the last observed pixel before
+// each word and the first after it, and the bits of a pixel's own word the
+// rest, so the row is read and written once, coalesced, with the samples
+// gathered from LDS.  Bound by memory latency, 2048 x 1000: 17.7 -> 11.4 us
+// (the per-thread chunks before read the row 32 bytes apart per lane).
 __global__ void __launch_bounds__(256) interp_fill_kernel(const float* __restrict__ y,
                                                           const uint32_t* __restrict__ mask, int words,
                                                           int Mk, int Nlat, float* __restrict__ out) {
-  __shared__ int lastc[256], firstc[256];
-  __shared__ short ridx[INTERP_MAX_MK];   // first observed pixel at or after m (Mk if none)
-  const int tid = threadIdx.x, nt = blockDim.x;
+  extern __shared__ float yr[];   // [Mk]
+  __shared__ uint32_t bits[256];
+  __shared__ int before[256], after[256];   // last observed pixel before the word, first after it (-1, Mk)
+  __shared__ int wl[4], wf[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t row = blockIdx.x;
-  const int64_t lat = row % Nlat;
-  const float* yr = y + row * Mk;
-  float* orow = out + row * Mk;
-  const int Q = (Mk + nt - 1) / nt;
-  const int c0 = min(tid * Q, Mk), c1 = min(c0 + Q, Mk);
-  int lastobs = -1, firstobs = Mk;
-  for (int m = c0; m < c1; ++m)
-    if (observed(mask, words, lat, m)) {
-      lastobs = m;
-      if (firstobs == Mk) firstobs = m;
-    }
-  lastc[tid] = lastobs;
-  firstc[tid] = firstobs;
+  const float* __restrict__ src = y + row * Mk;
+  float* __restrict__ dst = out + row * Mk;
+  if (!mask) {
+    for (int m = tid; m < Mk; m += 256) dst[m] = src[m];
+    return;
+  }
+  const uint32_t w = tid < words ? mask[(row % Nlat) * words + tid] : 0u;
+  for (int m = tid; m < Mk; m += 256) yr[m] = src[m];
+  int last = w ? tid * 32 + 31 - __clz((int)w) : -1, first = w ? tid * 32 + __ffs((int)w) - 1 : Mk;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {   // inclusive scans inside the wave
+    const int l = __shfl_up(last, o), f = __shfl_down(first, o);
+    if (lane >= o) last = max(last, l);
+    if (lane + o < 64) first = min(first, f);
+  }
+  const int lx = __shfl_up(last, 1), fx = __shfl_down(first, 1);   // exclusive
+  if (lane == 63) wl[wave] = last;
+  if (lane == 0) wf[wave] = first;
   __syncthreads();
-  // inclusive max-scan of lastc (left to right) and min-scan of firstc (right to left)
-  for (int off = 1; off < nt; off <<= 1) {
-    const int a = tid >= off ? lastc[tid - off] : -1;
-    const int b = tid + off < nt ? firstc[tid + off] : Mk;
-    __syncthreads();
-    lastc[tid] = max(lastc[tid], a);
-    firstc[tid] = min(firstc[tid], b);
-    __syncthreads();
+  int l = lane > 0 ? lx : -1, f = lane < 63 ? fx : Mk;
+  for (int v = 0; v < 4; ++v) {
+    if (v < wave) l = max(l, wl[v]);
+    if (v > wave) f = min(f, wf[v]);
   }
-  int right = tid + 1 < nt ? firstc[tid + 1] : Mk;   // first observed after this chunk
-  for (int m = c1 - 1; m >= c0; --m) {
-    if (observed(mask, words, lat, m)) right = m;
-    ridx[m] = (short)right;
-  }
-  int left = tid > 0 ? lastc[tid - 1] : -1;          // last observed before this chunk
-  for (int m = c0; m < c1; ++m) {
-    if (observed(mask, words, lat, m)) left = m;
-    const int R = ridx[m];
+  bits[tid] = w;
+  before[tid] = l;
+  after[tid] = f;
+  __syncthreads();
+  for (int m = tid; m < Mk; m += 256) {
+    const int i = m >> 5, b = m & 31;
+    const uint32_t lo = bits[i] & (0xffffffffu >> (31 - b)), hi = bits[i] & (0xffffffffu << b);
+    const int left = lo ? i * 32 + 31 - __clz((int)lo) : before[i], R = hi ? i * 32 + __ffs((int)hi) - 1 : after[i];
     float v;
     if (left == m) v = yr[m];
     else if (left < 0 && R >= Mk) v = 0.f;
@@ -93,7 +98,7 @@ __global__ void __launch_bounds__(256) interp_fill_kernel(const float* __restric
       const float yl = yr[left], yh = yr[R];
       v = fmaf((yh - yl) / (float)(R - left), (float)(m - left), yl);
     }
-    orow[m] = v;
+    dst[m] = v;
   }
 }
 
@@ -227,7 +232,7 @@ hipError_t launch_meas_to_complex(const float* y, const uint32_t* mask, int word
 
 hipError_t launch_interp_fill(const float* y, const uint32_t* mask, int words, int Mk, int Nlat, int64_t rows,
                               float* out, hipStream_t s) {
-  hipLaunchKernelGGL(interp_fill_kernel, dim3((unsigned)rows), dim3(256), 0, s, y, mask, words, Mk, Nlat, out);
+  hipLaunchKernelGGL(interp_fill_kernel, dim3((unsigned)rows), dim3(256), (size_t)Mk * sizeof(float), s, y, mask, words, Mk, Nlat, out);
   return hipGetLastError();
 }
 
