@@ -97,7 +97,7 @@ struct ColLds {
 template <int R, int CN>
 __device__ __forceinline__ void col_fwd_first(const ColArgs& a, const ColLds& l, const float2* s0, const float2* s1,
                                               int tid, int nthr) {
-  const int N = CN ? CN : a.n.Nz, nc = CN ? CN / 2 : a.n.nc;
+  const int N = CN ? CN : a.Nz, nc = CN ? CN / 2 : a.nc;
   const int nb = N / R;
   for (int item = tid; item < 2 * nb; item += nthr) {
     const int c = item & 1, j = item >> 1;
@@ -111,7 +111,7 @@ __device__ __forceinline__ void col_fwd_first(const ColArgs& a, const ColLds& l,
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       x[r] = src[depth(r)];
-      d[r] = a.n.deap[depth(r)];
+      d[r] = a.deap[depth(r)];
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = cscale(x[r], d[r]);
@@ -183,7 +183,7 @@ __device__ __forceinline__ void col_stage(const ColLds& l, int n, int ns, const 
 template <int R, int CN>
 __device__ __forceinline__ void col_inv_last(const ColArgs& a, const ColLds& l, const float2* __restrict__ tw,
                                              float2* d0, float2* d1, int tid, int nthr) {
-  const int N = CN ? CN : a.n.Nz, nc = CN ? CN / 2 : a.n.nc;
+  const int N = CN ? CN : a.Nz, nc = CN ? CN / 2 : a.nc;
   const int nb = N / R;   // = Ns
   for (int item = tid; item < 2 * nb; item += nthr) {
     const int c = item & 1, j = item >> 1;
@@ -205,7 +205,7 @@ __device__ __forceinline__ void col_inv_last(const ColArgs& a, const ColLds& l, 
     for (int r = 0; r < R; ++r) {
       int n = j + r * nb + nc;
       if (n >= N) n -= N;
-      const float d = a.n.deap[n];
+      const float d = a.deap[n];
       const float2 e = a.deap_odd[n];
       const float2 o = cmul(w[r], cconj(e));
       dst[n] = make_float2(fmaf(d, v[r].x, o.x), fmaf(d, v[r].y, o.y));
@@ -259,12 +259,12 @@ __device__ __forceinline__ void col_forward(const ColArgs& a, const ColLds& l, c
     const int last = a.f.ns - 1;
     for (int s = 1; s < last; ++s) {
 #define COL_MID(R) \
-  col_stage<R, MB, 0, 0, false, false, false>(l, a.n.Nz, a.f.sub[s], a.f.div_sub[s], a.tw + a.f.tw_off[s], tid, nthr)
+  col_stage<R, MB, 0, 0, false, false, false>(l, a.Nz, a.f.sub[s], a.f.div_sub[s], a.tw + a.f.tw_off[s], tid, nthr)
       COL_RADIX_SWITCH(a.f.radix[s], COL_MID)
 #undef COL_MID
     }
 #define COL_LAST(R) \
-  col_stage<R, MB, 0, 0, false, false, true>(l, a.n.Nz, a.f.sub[last], a.f.div_sub[last], a.tw + a.f.tw_off[last], tid, nthr)
+  col_stage<R, MB, 0, 0, false, false, true>(l, a.Nz, a.f.sub[last], a.f.div_sub[last], a.tw + a.f.tw_off[last], tid, nthr)
     COL_RADIX_SWITCH(a.f.radix[last], COL_LAST)
 #undef COL_LAST
   }
@@ -281,13 +281,13 @@ __device__ __forceinline__ void col_inverse(const ColArgs& a, const ColLds& l, f
     col_inv_last<8, CN>(a, l, a.tw + a.i.tw_off[2], d0, d1, tid, nthr);
   } else {
     const FastDiv one = a.i.div_sub[0];
-#define COL_FIRST(R) col_stage<R, MB, 0, 0, true, true, false>(l, a.n.Nz, 1, one, a.tw, tid, nthr)
+#define COL_FIRST(R) col_stage<R, MB, 0, 0, true, true, false>(l, a.Nz, 1, one, a.tw, tid, nthr)
     COL_RADIX_SWITCH(a.i.radix[0], COL_FIRST)
 #undef COL_FIRST
     const int last = a.i.ns - 1;
     for (int s = 1; s < last; ++s) {
 #define COL_MID(R) \
-  col_stage<R, MB, 0, 0, true, false, false>(l, a.n.Nz, a.i.sub[s], a.i.div_sub[s], a.tw + a.i.tw_off[s], tid, nthr)
+  col_stage<R, MB, 0, 0, true, false, false>(l, a.Nz, a.i.sub[s], a.i.div_sub[s], a.tw + a.i.tw_off[s], tid, nthr)
       COL_RADIX_SWITCH(a.i.radix[s], COL_MID)
 #undef COL_MID
     }
@@ -334,13 +334,13 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
   __shared__ double sh[16];
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int N = CN ? CN : a.n.Nz, K = 2 * N, Mk = a.n.Mk;
-  const int b = blockIdx.x / a.n.n_pairs;
-  const int4 pq = a.n.pairs[blockIdx.x - b * a.n.n_pairs];
-  const ColSpan sp = a.spans[blockIdx.x - b * a.n.n_pairs];
-  const int64_t item = (int64_t)b * (a.n.Nlat / a.n.Nx) * a.n.xs;
+  const int N = CN ? CN : a.Nz, K = 2 * N, Mk = a.Mk;
+  const int b = blockIdx.x / a.n_pairs;
+  const int4 pq = a.pairs[blockIdx.x - b * a.n_pairs];
+  const ColSpan sp = a.spans[blockIdx.x - b * a.n_pairs];
+  const int64_t item = (int64_t)b * a.item_cols;
   const int64_t col0 = (item + sp.x0) * N, col1 = (item + sp.x1) * N;
-  const int64_t slot = ((int64_t)b * a.n.n_half + pq.z) * Mk;
+  const int64_t slot = ((int64_t)b * a.n_half + pq.z) * Mk;
   const ColLds l{reinterpret_cast<float2*>(smem4), a.rs};
 
   if constexpr (MODE != COL_ADJ) col_forward<CN, MB>(a, l, X + col0, X + col1, tid, nthr);
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
   // the base cells u0 .. u0 + SPT - 1 of this thread and their samples
   const double q2 = sp.q2;
   const float bq = sp.beam;
-  const double ct = a.n.ct, k2min = 2.0 * a.n.k_min, dk2 = 2.0 * a.n.dk;
+  const double ct = a.ct, k2min = 2.0 * a.k_min, dk2 = 2.0 * a.dk;
   auto coord = [&](double m) __attribute__((always_inline)) {   // t(m); not positive for evanescent samples
     const double k = fma(m, dk2, k2min);
     return ct * col_sqrt(fma(k, k, -q2));
@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
     int m[SPT];
     float x[SPT];
     bool in[SPT];
-    const double ict = a.inv_ct, hik = 0.5 * a.inv_dk, k0 = -a.n.k_min * a.inv_dk;
+    const double ict = a.inv_ct, hik = 0.5 * a.inv_dk, k0 = -a.k_min * a.inv_dk;
     const double ub = (double)u0, bt0 = (ub + (0.5 - COL_EPS)) * ict, mlast = (double)(Mk - 1);
     double md[SPT], d[SPT];
     float2 ph[SPT], rv[SPT];
@@ -395,13 +395,13 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
         }
       }
     }
-    const float2* __restrict__ rin = MODE == COL_ADJ ? W + slot : pr.yh ? pr.yh + slot : a.n.phase;
+    const float2* __restrict__ rin = MODE == COL_ADJ ? W + slot : pr.yh ? pr.yh + slot : a.phase;
     const bool has_r = MODE == COL_ADJ || pr.yh;
 #pragma unroll
     for (int i = 0; i < SPT; ++i) {
       m[i] = (int)md[i];
       x[i] = (float)fma(2.0, d[i], -1.0);
-      ph[i] = at32(a.n.phase, m[i]);
+      ph[i] = at32(a.phase, m[i]);
       if constexpr (MODE != COL_FWD) {
         const float2 r = at32(rin, m[i]);
         rv[i] = make_float2(has_r ? r.x : 0.f, has_r ? r.y : 0.f);
@@ -413,7 +413,7 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
       const float xs = in[i] ? x[i] : 0.f, x2 = xs * xs;   // an empty cell's weights only have to be finite
 #pragma unroll
       for (int jj = 0; jj < J / 2; ++jj) {
-        const float* __restrict__ c = a.n.kbc + jj * 2 * KBH;
+        const float* __restrict__ c = a.kbc + jj * 2 * KBH;
         float e = c[KBH - 1], o = c[2 * KBH - 1];
 #pragma unroll
         for (int d = KBH - 2; d >= 0; --d) {
@@ -440,11 +440,11 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
       }
     }
     // the filter H(m, q) of the cells' samples (0 in empty cells)
-    if (a.n.df != 0.0) {   // defocus phase, reduced modulo 2 pi in FP64
+    if (a.df != 0.0) {   // defocus phase, reduced modulo 2 pi in FP64
 #pragma unroll
       for (int i = 0; i < SPT; ++i) {
         constexpr double two_pi = 6.283185307179586, inv_two_pi = 0.15915494309189535;
-        const double phase = coord((double)m[i]) * ict * a.n.df;
+        const double phase = coord((double)m[i]) * ict * a.df;
         const float f = (float)fma(-rint(phase * inv_two_pi), two_pi, phase);
         float sn, cs;
         sincosf(f, &sn, &cs);
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
       for (int i = 0; i < SPT; ++i)
         if (in[i]) out[m[i]] = rv[i];
       if (pq.w >= 0) {
-        float2* __restrict__ outp = W + ((int64_t)b * a.n.n_half + pq.w) * Mk;
+        float2* __restrict__ outp = W + ((int64_t)b * a.n_half + pq.w) * Mk;
 #pragma unroll
         for (int i = 0; i < SPT; ++i)
           if (in[i]) outp[m[i]] = cconj(rv[i]);
@@ -495,7 +495,7 @@ __global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs
   // evanescent samples (a prefix of the band, or all of it): W_h = 0, R^ = -yh with no column behind it
   if (MODE != COL_ADJ && sp.evan) {
     float2* __restrict__ out = W + slot;
-    float2* __restrict__ outp = (MODE == COL_FWD && pq.w >= 0) ? W + ((int64_t)b * a.n.n_half + pq.w) * Mk : nullptr;
+    float2* __restrict__ outp = (MODE == COL_FWD && pq.w >= 0) ? W + ((int64_t)b * a.n_half + pq.w) * Mk : nullptr;
     for (int m = tid; m < Mk; m += nthr) {
       if (coord((double)m) > 0.0) continue;
       if constexpr (MODE == COL_FWD) {
@@ -622,7 +622,7 @@ void fill_plan(int N, int ns, const int* radix, ColPlan* p, std::vector<float2>*
 template <int J, int MODE, int CN, int SPT, int MB>
 hipError_t col_launch_t(const ColArgs& a, const float2* X, float2* W, const PairRes& r, float2* Xo, int nthr,
                         hipStream_t s) {
-  const size_t lds = col_lds_bytes(a.n.Nz);
+  const size_t lds = col_lds_bytes(a.Nz);
   if (lds > 48 * 1024) {
     // once per instantiation (thread-safe initialisation of a local static)
     static const hipError_t set =
@@ -630,7 +630,7 @@ hipError_t col_launch_t(const ColArgs& a, const float2* X, float2* W, const Pair
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
     if (set != hipSuccess) return set;
   }
-  hipLaunchKernelGGL((column_pair_kernel<J, MODE, CN, SPT, MB>), dim3(a.n.n_pairs * (a.n.n_cols / a.n.Nlat)), dim3(nthr),
+  hipLaunchKernelGGL((column_pair_kernel<J, MODE, CN, SPT, MB>), dim3(a.n_pairs * a.batch), dim3(nthr),
                      lds, s, a, X, W, r, Xo);
   return hipGetLastError();
 }
@@ -641,9 +641,9 @@ hipError_t col_launch(const ColArgs& a, const float2* X, float2* W, const PairRe
   const int nt = col_threads(a, &spt, &mb);
   if (nt == 0) return hipErrorInvalidConfiguration;
 #define COL_T(J, CN, SPT, MB) col_launch_t<J, MODE, CN, SPT, MB>(a, X, W, r, Xo, nt, s)
-  if (a.n.J == 4) return COL_T(4, 0, 5, 2);
-  if (a.n.J == 8) return COL_T(8, 0, 5, 2);
-  const int cn = nt <= 512 ? a.n.Nz : 0;
+  if (a.J == 4) return COL_T(4, 0, 5, 2);
+  if (a.J == 8) return COL_T(8, 0, 5, 2);
+  const int cn = nt <= 512 ? a.Nz : 0;
   if (spt == 2) {
     switch (cn) {
       case 512: return COL_T(6, 512, 2, 1);
@@ -684,13 +684,13 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 // cells and one butterfly: there a pair's chain is what counts.
 int col_threads(const ColArgs& a, int* spt, int* mb) {
   int items = 0;
-  for (int s = 1; s < a.f.ns; ++s) items = std::max(items, 4 * (a.n.Nz / a.f.radix[s]));
-  const int64_t pairs = (int64_t)a.n.n_pairs * (a.n.n_cols / a.n.Nlat);
+  for (int s = 1; s < a.f.ns; ++s) items = std::max(items, 4 * (a.Nz / a.f.radix[s]));
+  const int64_t pairs = (int64_t)a.n_pairs * a.batch;
   for (int c : {2, 5}) {
-    if (c == 2 && (pairs > 256 || a.n.J != 6)) continue;
+    if (c == 2 && (pairs > 256 || a.J != 6)) continue;
     *spt = c;
-    *mb = c == 2 || a.n.Nz == 2048 ? 1 : 2;
-    const int nt = (std::max((items + *mb - 1) / *mb, (a.span + a.n.J - 1 + c - 1) / c) + 63) & ~63;
+    *mb = c == 2 || a.Nz == 2048 ? 1 : 2;
+    const int nt = (std::max((items + *mb - 1) / *mb, (a.span + a.J - 1 + c - 1) / c) + 63) & ~63;
     if (nt <= 1024) return nt;
   }
   return 0;
@@ -701,8 +701,8 @@ int col_threads(const ColArgs& a, int* spt, int* mb) {
 // the grid
 bool col_supported(const ColArgs& a) {
   int spt = 0, mb = 0;
-  return a.f.ns > 0 && a.n.K == 2 * a.n.Nz && 2.0 * a.n.ct * a.n.dk >= 1.0 - 1e-9 &&
-         a.span + a.n.J - 1 <= a.n.K && col_lds_bytes(a.n.Nz) <= 150 * 1024 && col_threads(a, &spt, &mb) > 0;
+  return a.f.ns > 0 && 2.0 * a.ct * a.dk >= 1.0 - 1e-9 &&
+         a.span + a.J - 1 <= 2 * a.Nz && col_lds_bytes(a.Nz) <= 150 * 1024 && col_threads(a, &spt, &mb) > 0;
 }
 
 hipError_t launch_col_fwd(const ColArgs& a, const float2* X1, float2* Wh, hipStream_t s) {
@@ -718,7 +718,7 @@ hipError_t launch_col_normal(const ColArgs& a, const float2* X1, const float2* y
   PairRes r{};
   r.yh = yh;
   r.partial = partial;
-  r.inv_nlat = 1.f / (float)a.n.Nlat;
-  r.nlat = (double)a.n.Nlat;
+  r.inv_nlat = 1.f / (float)a.nlat;
+  r.nlat = (double)a.nlat;
   return col_launch<COL_NORMAL>(a, X1, nullptr, r, X, s);
 }

@@ -11,8 +11,10 @@
 #define OCT_MAX_J 8
 // transform lengths with compile-time FFT code: oversampled grids (sigma = 2
 // on 512 .. 4096 depth samples) and lateral lengths of the common scan sizes
+// (radix-8 plans, and wide ones)
 #define OCT_CT_K_SIZES 1024, 2048, 4096, 8192
-#define OCT_CT_LAT_SIZES 64, 128, 256, 512, 1000, 1024
+#define OCT_CT_LAT_SIZES 64, 512
+#define OCT_CT_LAT_WIDE 128, 256, 1000, 1024
 
 // Division of a 32-bit unsigned by a runtime constant d >= 1 through a
 // multiply-high (Granlund-Montgomery round-up method): with l = ceil(log2 d),
@@ -48,6 +50,7 @@ struct FftDesc {
   FastDiv div_nb[OCT_MAX_STAGES];  // by n / radix (butterflies per row)
   FastDiv div_ns[OCT_MAX_STAGES];  // by ns
   int min_radix;
+  int wide;                      // radices up to 16 (one butterfly per thread)
   // Per-stage twiddle rows: stage s (radix R, sub-transform size Ns > 1) owns
   // Ns rows of fft_tw_pad(R) entries at tw_off[s]; row k holds
   // e^{-2 pi i r k / (Ns R)} for r = 1..R-1, zero-padded to an even count.
@@ -181,7 +184,15 @@ struct ColSpan {
   double q2;
 };
 struct ColArgs {
-  NufftArgs n;
+  int Nz, Mk, nc, J;
+  int nlat, batch;
+  int n_pairs, n_half;     // as NufftArgs'
+  int64_t item_cols;       // X's columns per batch item
+  double ct, df, k_min, dk;
+  const float2* phase;
+  const float* deap;
+  const float* kbc;
+  const int4* pairs;
   const ColSpan* spans;    // [n_pairs]
   ColPlan f, i;            // forward stages (smallest radix first) and inverse ones (the reverse)
   const float2* tw;        // twiddle rows of both
@@ -193,7 +204,8 @@ struct ColArgs {
 
 // Launchers (kernels in the .hip files; all asynchronous on `s`).
 hipError_t launch_lateral(LatMode mode, const LatArgs& a, hipStream_t s);
-int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* nthr, int* rowstride);
+int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride);
+bool lateral_wide(int L, int min_radix);
 hipError_t launch_nufft_fwd(const NufftArgs& a, const float2* X1, float2* W, hipStream_t s);
 hipError_t launch_nufft_adj(const NufftArgs& a, const float2* Rh, float2* X, hipStream_t s);
 size_t nufft_adj_lds_bytes(const NufftArgs& a);

@@ -51,6 +51,9 @@ __device__ __forceinline__ int fft_swz(int i) { return i ^ ((i >> 3) & 7); }
 // and the next stage reads through it.
 __device__ __forceinline__ int fft_swz2(int i) { return i ^ ((i >> 3) & 8); }
 
+// The first swizzle for a first radix of 16 (outputs 16 lanes apart).
+__device__ __forceinline__ int fft_swz16(int i) { return i ^ ((i >> 4) & 15); }
+
 // Element loop with batched loads: every thread first issues the loads of U
 // elements (indices clamped to a valid element, so each load is in bounds
 // and none waits on another), then consumes them in order.  A plain loop
@@ -301,12 +304,15 @@ template <bool INV> struct Dft<16, INV> : DftSquare<4, INV> {};
 // One Stockham stage over `nrows` transforms of length n stored at
 // buf[row * rowstride + i]; tw: this stage's twiddle rows (global memory).
 template <int R, int MAXB, bool INV>
-__device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride, int n, int Ns,
+__device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride, int n, int Ns, int R0,
                                           const FastDiv& dnb, const FastDiv& dns,
                                           const float2* __restrict__ tw, int tid, int nthr) {
   constexpr int NQ = fft_tw_pad(R) / 2;   // 16-byte loads per butterfly
   const int nb = n / R;
   const int total = nrows * nb;
+  // opaque: the caller's loop over stages would otherwise form the addresses
+  // of every radix ahead of the loop and spill them
+  asm volatile("" : "+v"(tid));
   float2 v[MAXB][R];
   float4 wq[MAXB][NQ];
   int off[MAXB], jj[MAXB], kk[MAXB];
@@ -323,9 +329,12 @@ __device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride,
         for (int q = 0; q < NQ; ++q) wq[b][q] = tp[q];
       }
       const float2* src = buf + row * rowstride;
-      if (Ns == 8) {   // second stage after a first radix-8 stage: swizzled layout
+      if (Ns == 8 && R0 == 8) {   // second stage after a first radix-8 stage: swizzled layout
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz(j + r * nb)];
+      } else if (Ns == 16 && R0 == 16) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz16(j + r * nb)];
       } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = src[j + r * nb];
@@ -355,6 +364,10 @@ __device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride,
         float2* dst = buf + off[b];
 #pragma unroll
         for (int r = 0; r < R; ++r) dst[fft_swz(j * R + r)] = v[b][r];
+      } else if (R == 16 && Ns == 1 && n > 16) {
+        float2* dst = buf + off[b];
+#pragma unroll
+        for (int r = 0; r < R; ++r) dst[fft_swz16(j * R + r)] = v[b][r];
       } else {
         float2* dst = buf + off[b] + (j - k) * R + k;
 #pragma unroll
@@ -373,23 +386,38 @@ struct FftCfg {
   static constexpr int MAXB = ONE ? 1 : 2;
 };
 
-template <bool ONE, bool INV>
+#define OCT_FFT_STAGE(R) \
+  fft_stage<R, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.radix[0], d.div_nb[s], d.div_ns[s], t, tid, nthr)
+template <bool ONE, bool INV, bool WIDE = false>
 __device__ __forceinline__ void fft_rows(float2* buf, int nrows, int rowstride, const FftDesc& d,
                                          const float2* __restrict__ tw, int tid, int nthr) {
   constexpr int MB = FftCfg<ONE>::MAXB;
   for (int s = 0; s < d.nstages; ++s) {
     const int Ns = d.ns[s];
     const float2* t = tw + d.tw_off[s];
+    if constexpr (WIDE) {
+      switch (d.radix[s]) {
+        case 6: OCT_FFT_STAGE(6); continue;
+        case 9: OCT_FFT_STAGE(9); continue;
+        case 10: OCT_FFT_STAGE(10); continue;
+        case 12: OCT_FFT_STAGE(12); continue;
+        case 14: OCT_FFT_STAGE(14); continue;
+        case 15: OCT_FFT_STAGE(15); continue;
+        case 16: OCT_FFT_STAGE(16); continue;
+        default: break;
+      }
+    }
     switch (d.radix[s]) {
-      case 8: fft_stage<8, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
-      case 4: fft_stage<4, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
-      case 2: fft_stage<2, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
-      case 5: fft_stage<5, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
-      case 3: fft_stage<3, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
-      default: fft_stage<7, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.div_nb[s], d.div_ns[s], t, tid, nthr); break;
+      case 8: OCT_FFT_STAGE(8); break;
+      case 4: OCT_FFT_STAGE(4); break;
+      case 2: OCT_FFT_STAGE(2); break;
+      case 5: OCT_FFT_STAGE(5); break;
+      case 3: OCT_FFT_STAGE(3); break;
+      default: OCT_FFT_STAGE(7); break;
     }
   }
 }
+#undef OCT_FFT_STAGE
 
 // ---------------------------------------------------------------------------
 // Compile-time transform lengths.  For the lengths a kernel instantiates, the
@@ -423,13 +451,48 @@ constexpr CtPlan ct_plan(int n) {
     while (m % odd[i] == 0) { m /= odd[i]; p.r[p.ns++] = odd[i]; }
   return p;
 }
+// The wide plan: as few stages as radices up to 16 allow, in increasing order,
+// with the largest first radix among those.  An empty plan: more than four
+// stages.
+constexpr bool ct_wide_rec(int n, int s, int ns, int lo, int* cur, int* best, bool found) {
+  constexpr int set[] = {2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16};
+  if (s == ns) {
+    if (n != 1) return found;
+    if (found) {
+      int i = 0;
+      while (i < ns && cur[i] == best[i]) ++i;
+      if (i == ns || cur[i] < best[i]) return true;
+    }
+    for (int i = 0; i < ns; ++i) best[i] = cur[i];
+    return true;
+  }
+  for (int r : set)
+    if (r >= lo && n % r == 0) {
+      cur[s] = r;
+      found = ct_wide_rec(n / r, s + 1, ns, r, cur, best, found);
+    }
+  return found;
+}
+constexpr CtPlan ct_wide(int n) {
+  CtPlan p{};
+  for (int ns = 1; ns <= 4; ++ns) {
+    int cur[4] = {}, best[4] = {};
+    if (!ct_wide_rec(n, 0, ns, 2, cur, best, false)) continue;
+    p.ns = ns;
+    for (int i = 0; i < ns; ++i) p.r[i] = best[i];
+    return p;
+  }
+  return p;
+}
+constexpr CtPlan ct_plan_of(int n, bool wide) { return wide ? ct_wide(n) : ct_plan(n); }
 constexpr int ct_ns_before(const CtPlan& p, int s) {
   int v = 1;
   for (int i = 0; i < s; ++i) v *= p.r[i];
   return v;
 }
 
-template <int R, int N, int NS, int MAXB, bool INV, bool SWZ2_IN = false, bool SWZ2_OUT = false>
+// SWZ16: the first radix is 16
+template <int R, int N, int NS, int MAXB, bool INV, bool SWZ2_IN = false, bool SWZ2_OUT = false, bool SWZ16 = false>
 __device__ __forceinline__ void fft_stage_ct(float2* buf, int nrows, int rowstride,
                                              const float2* __restrict__ tw, int tid, int nthr) {
   constexpr int NQ = fft_tw_pad(R) / 2;
@@ -455,6 +518,10 @@ __device__ __forceinline__ void fft_stage_ct(float2* buf, int nrows, int rowstri
         const float2* src = buf + base[b];
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz(j + r * nb)];
+      } else if (SWZ16 && NS == 16) {
+        const float2* src = buf + base[b];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz16(j + r * nb)];
       } else if (SWZ2_IN) {   // after a swizzled second stage
         const float2* src = buf + base[b];
 #pragma unroll
@@ -487,6 +554,10 @@ __device__ __forceinline__ void fft_stage_ct(float2* buf, int nrows, int rowstri
         float2* dst = buf + base[b];
 #pragma unroll
         for (int r = 0; r < R; ++r) dst[fft_swz(j * R + r)] = v[b][r];
+      } else if (SWZ16 && NS == 1 && N > 16) {
+        float2* dst = buf + base[b];
+#pragma unroll
+        for (int r = 0; r < R; ++r) dst[fft_swz16(j * R + r)] = v[b][r];
       } else if (SWZ2_OUT) {
         float2* dst = buf + base[b];
         const int o = (j - k) * R + k;
@@ -505,28 +576,28 @@ __device__ __forceinline__ void fft_stage_ct(float2* buf, int nrows, int rowstri
 // Stage S of the plan of length N writes through fft_swz2 when it is a
 // radix-8 stage of sub-transform size 8 and another stage follows; stage S
 // reads through it when stage S - 1 did.
-template <int N, int S>
+template <int N, int S, bool WIDE = false>
 constexpr bool ct_swz2_out() {
-  constexpr CtPlan P = ct_plan(N);
+  constexpr CtPlan P = ct_plan_of(N, WIDE);
   return S >= 0 && S + 1 < P.ns && P.r[S] == 8 && ct_ns_before(P, S) == 8;
 }
 
 // stages S..E-1 of the compile-time plan of length N
-template <int N, int S, int E, int MAXB, bool INV>
+template <int N, int S, int E, int MAXB, bool INV, bool WIDE = false>
 __device__ __forceinline__ void fft_ct_stage_range(float2* buf, int nrows, int rowstride, const FftDesc& d,
                                                    const float2* __restrict__ tw, int tid, int nthr) {
-  constexpr CtPlan P = ct_plan(N);
+  constexpr CtPlan P = ct_plan_of(N, WIDE);
   if constexpr (S < E) {
-    fft_stage_ct<P.r[S], N, ct_ns_before(P, S), MAXB, INV, ct_swz2_out<N, S - 1>(), ct_swz2_out<N, S>()>(
-        buf, nrows, rowstride, tw + d.tw_off[S], tid, nthr);
-    fft_ct_stage_range<N, S + 1, E, MAXB, INV>(buf, nrows, rowstride, d, tw, tid, nthr);
+    fft_stage_ct<P.r[S], N, ct_ns_before(P, S), MAXB, INV, ct_swz2_out<N, S - 1, WIDE>(), ct_swz2_out<N, S, WIDE>(),
+                 P.r[0] == 16>(buf, nrows, rowstride, tw + d.tw_off[S], tid, nthr);
+    fft_ct_stage_range<N, S + 1, E, MAXB, INV, WIDE>(buf, nrows, rowstride, d, tw, tid, nthr);
   }
 }
 
-template <int N, int S, int MAXB, bool INV>
+template <int N, int S, int MAXB, bool INV, bool WIDE = false>
 __device__ __forceinline__ void fft_ct_stages(float2* buf, int nrows, int rowstride, const FftDesc& d,
                                               const float2* __restrict__ tw, int tid, int nthr) {
-  fft_ct_stage_range<N, S, ct_plan(N).ns, MAXB, INV>(buf, nrows, rowstride, d, tw, tid, nthr);
+  fft_ct_stage_range<N, S, ct_plan_of(N, WIDE).ns, MAXB, INV, WIDE>(buf, nrows, rowstride, d, tw, tid, nthr);
 }
 
 // fft_rows with a compile-time path for each length in SIZES (the generic
@@ -542,3 +613,13 @@ __device__ __forceinline__ void fft_rows_sized(float2* buf, int nrows, int rowst
   if (!done) fft_rows<ONE, INV>(buf, nrows, rowstride, d, tw, tid, nthr);
 }
 
+// The same for wide plans (one butterfly per thread); SIZES' plans are wide.
+template <bool INV, int... SIZES>
+__device__ __forceinline__ void fft_rows_wide(float2* buf, int nrows, int rowstride, const FftDesc& d,
+                                              const float2* __restrict__ tw, int tid, int nthr) {
+  bool done = false;
+  ((!done && d.n == SIZES ? (fft_ct_stages<SIZES, 0, 1, INV, true>(buf, nrows, rowstride, d, tw, tid, nthr),
+                              done = true)
+                          : false), ...);
+  if (!done) fft_rows<true, INV, true>(buf, nrows, rowstride, d, tw, tid, nthr);
+}

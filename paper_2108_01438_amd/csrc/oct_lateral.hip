@@ -13,6 +13,7 @@
 //     the next iteration's forward lateral transform.
 #include "oct_fft.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -105,7 +106,18 @@ template <> struct LatOff<false> {
   template <typename T> __device__ static T* at(T* origin, type o) { return origin + o; }
 };
 
-template <int MODE, bool ONE, bool OFF32>
+// Transform variants: a radix-8 plan with two butterflies per thread or one, and
+// a wide plan (radices up to 16, one butterfly per thread).
+enum { FFT_TWO = 0, FFT_ONE = 1, FFT_WIDE = 2 };
+
+template <int VAR, bool INV>
+__device__ __forceinline__ void lat_fft(float2* lds, int nrows, int rs, const FftDesc& fd, const float2* tw, int tid,
+                                        int nthr) {
+  if constexpr (VAR == FFT_WIDE) fft_rows_wide<INV, OCT_CT_LAT_WIDE>(lds, nrows, rs, fd, tw, tid, nthr);
+  else fft_rows_sized<VAR == FFT_ONE, INV, OCT_CT_LAT_SIZES>(lds, nrows, rs, fd, tw, tid, nthr);
+}
+
+template <int MODE, int VAR, bool OFF32>
 __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
   extern __shared__ float2 lds[];
   __shared__ double red[16];
@@ -335,8 +347,8 @@ __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
     __syncthreads();
   }
 
-  if (a.inverse) fft_rows_sized<ONE, true, OCT_CT_LAT_SIZES>(lds, nrow_t, rs, a.fd, twl, tid, nthr);
-  else fft_rows_sized<ONE, false, OCT_CT_LAT_SIZES>(lds, nrow_t, rs, a.fd, twl, tid, nthr);
+  if (a.inverse) lat_fft<VAR, true>(lds, nrow_t, rs, a.fd, twl, tid, nthr);
+  else lat_fft<VAR, false>(lds, nrow_t, rs, a.fd, twl, tid, nthr);
 
   if (MODE == LAT_FFT || MODE == LAT_ADJ_MEAS) {
     const int Lout = (MODE == LAT_ADJ_MEAS && half) ? Lh : L;   // spectra of real rows: l <= L/2 suffices
@@ -409,7 +421,7 @@ __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
         lds[p_own * rs + l] = make_float2(ra, rb);
       });
     __syncthreads();
-    fft_rows_sized<ONE, false, OCT_CT_LAT_SIZES>(lds, H, rs, a.fd, twl, tid, nthr);
+    lat_fft<VAR, false>(lds, H, rs, a.fd, twl, tid, nthr);
     if (t_ok)
       lat_each(l_own, LS, half ? Lh : L, t_own, [&](int l, Off o) {
         *at(dsth_o, o) = cscale(unpack_real_pair(lds, rs, L, H, t_own, l), a.scale2);
@@ -431,7 +443,7 @@ __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
         lds[t_own * rs + l] = make_float2(r, 0.f);
       });
     __syncthreads();
-    fft_rows_sized<ONE, false, OCT_CT_LAT_SIZES>(lds, T, rs, a.fd, twl, tid, nthr);
+    lat_fft<VAR, false>(lds, T, rs, a.fd, twl, tid, nthr);
     if (t_ok)
       lat_each(l_own, LS, half ? Lh : L, t_own, [&](int l, Off o) {
         *at(dsth_o, o) = cscale(lds[t_own * rs + l], a.scale2);
@@ -468,7 +480,7 @@ __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
         lds[t_own * rs + l] = xn;
       });
     __syncthreads();
-    fft_rows_sized<ONE, false, OCT_CT_LAT_SIZES>(lds, T, rs, a.fd, twl, tid, nthr);
+    lat_fft<VAR, false>(lds, T, rs, a.fd, twl, tid, nthr);
     if (t_ok)
       lat_each(l_own, LS, L, t_own, [&](int l, Off o) { *at(dst_o, o) = lds[t_own * rs + l]; });
     if (a.partial) {
@@ -481,74 +493,95 @@ __global__ void __launch_bounds__(1024) lat_kernel(LatArgs a) {
 
 }  // namespace
 
-// Rows per tile and threads per block: the tile (T rows of L complex) stays
-// within 64 KB of LDS and every FFT stage fits 2 butterflies per thread; on
-// images too small to give every CU a tile, the tiles narrow (to two rows at
-// least) until they do.
-int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* nthr, int* rowstride) {
+// Threads of a tile of T rows.  Radix-8 plans: a power of two, every stage's
+// butterflies at most two per thread.  Wide plans: every butterfly its own
+// thread, and at most eight elements per thread, so that the loads a transform
+// does not wait for fit their registers.  0: none.
+static int lateral_threads(const FftDesc& fd, int T) {
+  const int64_t bf = (int64_t)T * (fd.n / fd.min_radix), n = (int64_t)T * fd.n;
+  if (bf > (fd.wide ? 1024 : 2048)) return 0;
+  if (fd.wide) return std::max(256, (int)((std::min<int64_t>(std::max(bf, (n + 7) / 8), 1024) + 63) & ~63));
+  int nt = 256;
+  while (bf > 2 * nt) nt <<= 1;
+  return nt;
+}
+
+// Rows per tile: the tile (T rows of L complex) stays within 64 KB of LDS and
+// every FFT stage fits the threads; on images too small to give every CU a
+// tile, the tiles narrow (to two rows at least) until they do.
+int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride) {
   const int rs = (lg.L % 2 == 0) ? lg.L + 1 : lg.L;  // odd stride spreads LDS banks
-  const int mb = fft_maxb(fd);
   const int64_t budget = 65280;   // tile within 64 KB
   int T = 32;
   while (T > 1 && (int64_t)T * rs * 8 > budget) T >>= 1;
   while (T > 1 && T > lg.rows) T >>= 1;
   for (; T >= 1; T >>= 1) {
-    const int64_t bf = (int64_t)T * lg.L / fd.min_radix;
-    for (int nt = 256; nt <= 1024; nt <<= 1) {
-      if (bf <= mb * nt && (int64_t)T * rs * 8 <= budget) {
-        // small images: narrower tiles while the largest would leave CUs
-        // without a tile (the pass is then one tile's chain long, and a
-        // narrower tile's chain is shorter); down to row pairs
-        while (T > 2 && (int64_t)lg.n_lines * ((lg.rows + T - 1) / T) < 256) T >>= 1;
-        *nthr = nt;
-        *rowstride = rs;
-        return T;
-      }
+    if (lateral_threads(fd, T) > 0 && (int64_t)T * rs * 8 <= budget) {
+      // small images: narrower tiles while the largest would leave CUs
+      // without a tile (the pass is then one tile's chain long, and a
+      // narrower tile's chain is shorter); down to row pairs
+      while (T > 2 && (int64_t)lg.n_lines * ((lg.rows + T - 1) / T) < 256) T >>= 1;
+      *rowstride = rs;
+      return T;
     }
   }
   return 0;
 }
 
-template <int MODE, bool ONE, bool OFF32>
+// Whether a length takes its wide plan: if the widest tile it allows still has
+// a thread for every butterfly (the other plan runs two per thread instead of
+// narrowing the tile).
+bool lateral_wide(int L, int min_radix) {
+  const int rs = (L % 2 == 0) ? L + 1 : L;
+  int T = 32;
+  while (T > 1 && (int64_t)T * rs * 8 > 65280) T >>= 1;
+  return (int64_t)T * (L / min_radix) <= 1024;
+}
+
+template <int MODE, int VAR, bool OFF32>
 hipError_t launch_lateral_m(const LatArgs& a, int nthr, hipStream_t s) {
   const size_t lds = ((size_t)lat_tile_f2(a.T, a.rowstride) + (size_t)a.fd.tw_total) * sizeof(float2);
   if (lds > 64 * 1024) {
     // once per instantiation (thread-safe initialisation of a local static)
-    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&lat_kernel<MODE, ONE, OFF32>),
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(&lat_kernel<MODE, VAR, OFF32>),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 2048);
     if (set != hipSuccess) return set;
   }
-  hipLaunchKernelGGL((lat_kernel<MODE, ONE, OFF32>), dim3((a.lg.n_lines * a.n_tiles + 7) & ~7), dim3(nthr), lds, s,
+  hipLaunchKernelGGL((lat_kernel<MODE, VAR, OFF32>), dim3((a.lg.n_lines * a.n_tiles + 7) & ~7), dim3(nthr), lds, s,
                      a);
   return hipGetLastError();
 }
 
-template <bool ONE, bool OFF32>
+template <int VAR, bool OFF32>
 hipError_t launch_lateral_t(LatMode mode, const LatArgs& a, int nthr, hipStream_t s) {
   switch (mode) {
-    case LAT_FFT: return launch_lateral_m<LAT_FFT, ONE, OFF32>(a, nthr, s);
-    case LAT_FWD_MEAS: return launch_lateral_m<LAT_FWD_MEAS, ONE, OFF32>(a, nthr, s);
-    case LAT_ADJ_MEAS: return launch_lateral_m<LAT_ADJ_MEAS, ONE, OFF32>(a, nthr, s);
-    case LAT_NORMAL: return launch_lateral_m<LAT_NORMAL, ONE, OFF32>(a, nthr, s);
-    case LAT_UPDATE: return launch_lateral_m<LAT_UPDATE, ONE, OFF32>(a, nthr, s);
-    case LAT_UPDATE_L1: return launch_lateral_m<LAT_UPDATE_L1, ONE, OFF32>(a, nthr, s);
-    case LAT_RESID: return launch_lateral_m<LAT_RESID, ONE, OFF32>(a, nthr, s);
+    case LAT_FFT: return launch_lateral_m<LAT_FFT, VAR, OFF32>(a, nthr, s);
+    case LAT_FWD_MEAS: return launch_lateral_m<LAT_FWD_MEAS, VAR, OFF32>(a, nthr, s);
+    case LAT_ADJ_MEAS: return launch_lateral_m<LAT_ADJ_MEAS, VAR, OFF32>(a, nthr, s);
+    case LAT_NORMAL: return launch_lateral_m<LAT_NORMAL, VAR, OFF32>(a, nthr, s);
+    case LAT_UPDATE: return launch_lateral_m<LAT_UPDATE, VAR, OFF32>(a, nthr, s);
+    case LAT_UPDATE_L1: return launch_lateral_m<LAT_UPDATE_L1, VAR, OFF32>(a, nthr, s);
+    case LAT_RESID: return launch_lateral_m<LAT_RESID, VAR, OFF32>(a, nthr, s);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_lateral(LatMode mode, const LatArgs& a, hipStream_t s) {
-  const int64_t bf = (int64_t)a.T * (a.fd.n / a.fd.min_radix);
-  const int mb = fft_maxb(a.fd);
-  int nthr = 256;
-  while (nthr < 1024 && bf > (int64_t)mb * nthr) nthr <<= 1;
-  if (bf > (int64_t)mb * nthr) return hipErrorInvalidConfiguration;
+  const int nthr = lateral_threads(a.fd, a.T);
   // a thread owns one tile row: the threads must be a multiple of the rows
-  if (nthr % a.T != 0) return hipErrorInvalidConfiguration;
+  if (nthr == 0 || nthr % a.T != 0) return hipErrorInvalidConfiguration;
   // 32-bit byte offsets inside a tile when its span (lateral stride times the
   // laterals, plus the rows) stays below 4 GiB
   const bool off32 = ((int64_t)(a.lg.L - 1) * a.lg.es + a.T) * (int64_t)sizeof(float2) < ((int64_t)1 << 32);
-  if (fft_one(a.fd, a.T, nthr))
-    return off32 ? launch_lateral_t<true, true>(mode, a, nthr, s) : launch_lateral_t<true, false>(mode, a, nthr, s);
-  return off32 ? launch_lateral_t<false, true>(mode, a, nthr, s) : launch_lateral_t<false, false>(mode, a, nthr, s);
+  switch (a.fd.wide ? FFT_WIDE : fft_one(a.fd, a.T, nthr) ? FFT_ONE : FFT_TWO) {
+    case FFT_WIDE:
+      return off32 ? launch_lateral_t<FFT_WIDE, true>(mode, a, nthr, s)
+                   : launch_lateral_t<FFT_WIDE, false>(mode, a, nthr, s);
+    case FFT_ONE:
+      return off32 ? launch_lateral_t<FFT_ONE, true>(mode, a, nthr, s)
+                   : launch_lateral_t<FFT_ONE, false>(mode, a, nthr, s);
+    default:
+      return off32 ? launch_lateral_t<FFT_TWO, true>(mode, a, nthr, s)
+                   : launch_lateral_t<FFT_TWO, false>(mode, a, nthr, s);
+  }
 }
