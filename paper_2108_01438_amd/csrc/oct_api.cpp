@@ -146,21 +146,16 @@ bool factorize(int n, FftDesc& d) {
   return m == 1 && plan_stages(n, d, rad, 0);
 }
 
-// Lateral lengths: the wide plan where it has fewer stages and its tile suits
-// it (lateral_wide).  Fewer stages: 26.0 -> 19.2 us for the forward pass of
-// 1400 x 1120, 544 -> 513 us a pass of the 2048 x 256 x 256 volume; with as
-// many, its one butterfly per thread costs resident tiles (26.4 -> 28.8 us for
-// the seam of 8 x 1024 x 512).
-bool factorize_lateral(int n, FftDesc& d) {
-  if (!factorize(n, d)) return false;
-  const CtPlan c = ct_wide(n);
-  if (c.ns == 0 || c.ns >= d.nstages) return true;
-  FftDesc w;
+// The wide plan of a lateral length, where it has fewer stages than the
+// radix-8 plan d: 26.0 -> 19.2 us for the forward pass of 1400 x 1120, 544 ->
+// 513 us a pass of the 2048 x 256 x 256 volume; with as many, its one
+// butterfly per thread costs resident tiles (26.4 -> 28.8 us for the seam of
+// 8 x 1024 x 512).
+bool factorize_wide(const FftDesc& d, FftDesc& w) {
+  const CtPlan c = ct_wide(d.n);
   std::memset(&w, 0, sizeof(w));
-  w.n = n;
-  if (!plan_stages(n, w, std::vector<int>(c.r, c.r + c.ns), 1) || !lateral_wide(n, w.min_radix)) return true;
-  d = w;
-  return true;
+  w.n = d.n;
+  return c.ns > 0 && c.ns < d.nstages && plan_stages(d.n, w, std::vector<int>(c.r, c.r + c.ns), 1);
 }
 
 // Per-stage twiddle rows of FftDesc (layout in oct_common.h), built in FP64.
@@ -328,8 +323,8 @@ oct_status unsupported_sizes(const oct_geometry* g) {
   FftDesc d;
   if (K > 8192) return fail(OCT_E_UNSUPPORTED, "oversampled grid K > 8192");
   if (!factorize((int)K, d)) return fail(OCT_E_UNSUPPORTED, "K has a prime factor above 7");
-  if (g->n_x > 4096 || !factorize_lateral((int)g->n_x, d)) return fail(OCT_E_UNSUPPORTED, "n_x must be 7-smooth and <= 4096");
-  if (g->lateral_dims == 2 && (g->n_y > 4096 || !factorize_lateral((int)g->n_y, d)))
+  if (g->n_x > 4096 || !factorize((int)g->n_x, d)) return fail(OCT_E_UNSUPPORTED, "n_x must be 7-smooth and <= 4096");
+  if (g->lateral_dims == 2 && (g->n_y > 4096 || !factorize((int)g->n_y, d)))
     return fail(OCT_E_UNSUPPORTED, "n_y must be 7-smooth and <= 4096");
   if (g->n_k > 8192) return fail(OCT_E_UNSUPPORTED, "n_k > 8192");
   if (g->model == OCT_MODEL_LITERAL) {
@@ -342,18 +337,12 @@ oct_status unsupported_sizes(const oct_geometry* g) {
   }
   // the kernels' compile-time FFT paths must use the radix plan of factorize
   {
-    constexpr int sizes[] = {OCT_CT_K_SIZES, OCT_CT_LAT_SIZES, OCT_CT_LAT_WIDE};
-    constexpr int n_wide = sizeof((int[]){OCT_CT_LAT_WIDE}) / sizeof(int);
-    constexpr int n_sizes = sizeof(sizes) / sizeof(int);
-    constexpr int n_k_sizes = sizeof((int[]){OCT_CT_K_SIZES}) / sizeof(int);
-    for (int i = 0; i < n_sizes; ++i) {
-      const int n = sizes[i];
-      const bool lat = i >= n_k_sizes, wide = i >= n_sizes - n_wide;
+    constexpr int sizes[] = {OCT_CT_K_SIZES, OCT_CT_LAT_SIZES};
+    for (int n : sizes) {
       FftDesc f;
-      if (lat) factorize_lateral(n, f);
-      else factorize(n, f);
-      const CtPlan c = ct_plan_of(n, wide);
-      bool same = c.ns == f.nstages && (f.wide != 0) == wide;
+      factorize(n, f);
+      const CtPlan c = ct_plan(n);
+      bool same = c.ns == f.nstages;
       for (int s = 0; same && s < c.ns; ++s) same = c.r[s] == f.radix[s];
       if (!same) return fail(OCT_E_UNSUPPORTED, "internal: compile-time FFT plan differs from the host plan");
     }
@@ -964,8 +953,14 @@ oct_status oct_plan_create(const oct_geometry* g, const uint8_t* mask, oct_plan_
   p->df = p->zf - p->nc * p->dz;
   if (std::fabs(p->df) < 1e-12 * std::max(1.0, std::fabs(p->zf))) p->df = 0.0;
   factorize((int)p->K, p->fK);
-  factorize_lateral((int)p->Nx, p->fX);
-  factorize_lateral((int)p->Ny, p->fY);
+  factorize((int)p->Nx, p->fX);
+  factorize((int)p->Ny, p->fY);
+  {
+    FftDesc w;
+    const int rows = (int)std::min(p->Nz, p->Mk);
+    if (factorize_wide(p->fX, w) && lateral_wide(lines_x(p, rows), w)) p->fX = w;
+    if (factorize_wide(p->fY, w) && lateral_wide(lines_y(p, rows), w)) p->fY = w;
+  }
 
   oct_status st = OCT_OK;
   auto cleanup = [&](oct_status e) {

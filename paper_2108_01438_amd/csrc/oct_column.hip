@@ -327,7 +327,7 @@ enum { COL_FWD = 0, COL_ADJ = 1, COL_NORMAL = 2 };
 // it writes them), the pair's share of ||r||^2 by Parseval into r.partial.
 // Up to MB butterflies per thread in the stages that run in place.
 template <int J, int MODE, int CN, int SPT, int MB>
-__global__ void __launch_bounds__(CN ? 512 : 1024, 4) column_pair_kernel(ColArgs a, const float2* X, float2* W,
+__global__ void __launch_bounds__(CN && SPT != 2 ? 512 : 1024, 4) column_pair_kernel(ColArgs a, const float2* X, float2* W,
                                                                        PairRes pr, float2* Xo) {
   extern __shared__ float4 smem4[];
   __shared__ float4 edge[16][J - 1];
@@ -643,14 +643,14 @@ hipError_t col_launch(const ColArgs& a, const float2* X, float2* W, const PairRe
 #define COL_T(J, CN, SPT, MB) col_launch_t<J, MODE, CN, SPT, MB>(a, X, W, r, Xo, nt, s)
   if (a.J == 4) return COL_T(4, 0, 5, 2);
   if (a.J == 8) return COL_T(8, 0, 5, 2);
-  const int cn = nt <= 512 ? a.Nz : 0;
   if (spt == 2) {
-    switch (cn) {
+    switch (a.Nz) {
       case 512: return COL_T(6, 512, 2, 1);
+      case 1024: return COL_T(6, 1024, 2, 1);
       default: return COL_T(6, 0, 2, 1);
     }
   }
-  switch (cn) {
+  switch (nt <= 512 ? a.Nz : 0) {
     case 512: return COL_T(6, 512, 5, 2);
     case 1024: return COL_T(6, 1024, 5, 2);
     case 2048: return COL_T(6, 2048, 5, 1);
@@ -680,18 +680,19 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 // Threads per pair, base cells per thread and butterflies per thread.  Five
 // cells share ten-cell windows between five samples; with two butterflies per
 // thread the stages that run in place take no more threads than the cells do,
-// and more pairs share a CU.  Launches that leave CUs without a pair take two
-// cells and one butterfly: there a pair's chain is what counts.
+// and more pairs share a CU.  Launches of at most eight waves a CU, where a
+// pair's chain is what counts, take two cells and one butterfly (forward of
+// 245 x 600, 301 pairs: 22.2 us a call against 24.4).
 int col_threads(const ColArgs& a, int* spt, int* mb) {
   int items = 0;
   for (int s = 1; s < a.f.ns; ++s) items = std::max(items, 4 * (a.Nz / a.f.radix[s]));
   const int64_t pairs = (int64_t)a.n_pairs * a.batch;
   for (int c : {2, 5}) {
-    if (c == 2 && (pairs > 256 || a.J != 6)) continue;
+    if (c == 2 && a.J != 6) continue;
     *spt = c;
     *mb = c == 2 || a.Nz == 2048 ? 1 : 2;
     const int nt = (std::max((items + *mb - 1) / *mb, (a.span + a.J - 1 + c - 1) / c) + 63) & ~63;
-    if (nt <= 1024) return nt;
+    if (nt <= 1024 && (c != 2 || pairs * (nt / 64) <= 8 * 256)) return nt;
   }
   return 0;
 }

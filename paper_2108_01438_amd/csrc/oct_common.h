@@ -13,7 +13,7 @@
 // on 512 .. 4096 depth samples) and lateral lengths of the common scan sizes
 // (radix-8 plans, and wide ones)
 #define OCT_CT_K_SIZES 1024, 2048, 4096, 8192
-#define OCT_CT_LAT_SIZES 64, 512
+#define OCT_CT_LAT_SIZES 64, 128, 256, 512, 1000, 1024
 #define OCT_CT_LAT_WIDE 128, 256, 1000, 1024
 
 // Division of a 32-bit unsigned by a runtime constant d >= 1 through a
@@ -205,7 +205,7 @@ struct ColArgs {
 // Launchers (kernels in the .hip files; all asynchronous on `s`).
 hipError_t launch_lateral(LatMode mode, const LatArgs& a, hipStream_t s);
 int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride);
-bool lateral_wide(int L, int min_radix);
+bool lateral_wide(const LineGeom& lg, const FftDesc& fd);
 hipError_t launch_nufft_fwd(const NufftArgs& a, const float2* X1, float2* W, hipStream_t s);
 hipError_t launch_nufft_adj(const NufftArgs& a, const float2* Rh, float2* X, hipStream_t s);
 size_t nufft_adj_lds_bytes(const NufftArgs& a);

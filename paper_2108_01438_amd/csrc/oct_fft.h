@@ -303,7 +303,7 @@ template <bool INV> struct Dft<16, INV> : DftSquare<4, INV> {};
 
 // One Stockham stage over `nrows` transforms of length n stored at
 // buf[row * rowstride + i]; tw: this stage's twiddle rows (global memory).
-template <int R, int MAXB, bool INV>
+template <int R, int MAXB, bool INV, bool WIDE>
 __device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride, int n, int Ns, int R0,
                                           const FastDiv& dnb, const FastDiv& dns,
                                           const float2* __restrict__ tw, int tid, int nthr) {
@@ -311,8 +311,8 @@ __device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride,
   const int nb = n / R;
   const int total = nrows * nb;
   // opaque: the caller's loop over stages would otherwise form the addresses
-  // of every radix ahead of the loop and spill them
-  asm volatile("" : "+v"(tid));
+  // of every wide radix ahead of the loop and spill them
+  if (WIDE) asm volatile("" : "+v"(tid));
   float2 v[MAXB][R];
   float4 wq[MAXB][NQ];
   int off[MAXB], jj[MAXB], kk[MAXB];
@@ -329,10 +329,10 @@ __device__ __forceinline__ void fft_stage(float2* buf, int nrows, int rowstride,
         for (int q = 0; q < NQ; ++q) wq[b][q] = tp[q];
       }
       const float2* src = buf + row * rowstride;
-      if (Ns == 8 && R0 == 8) {   // second stage after a first radix-8 stage: swizzled layout
+      if (Ns == 8 && (!WIDE || R0 == 8)) {   // second stage after a first radix-8 stage: swizzled layout
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz(j + r * nb)];
-      } else if (Ns == 16 && R0 == 16) {
+      } else if (WIDE && Ns == 16 && R0 == 16) {
 #pragma unroll
         for (int r = 0; r < R; ++r) v[b][r] = src[fft_swz16(j + r * nb)];
       } else {
@@ -387,7 +387,7 @@ struct FftCfg {
 };
 
 #define OCT_FFT_STAGE(R) \
-  fft_stage<R, MB, INV>(buf, nrows, rowstride, d.n, Ns, d.radix[0], d.div_nb[s], d.div_ns[s], t, tid, nthr)
+  fft_stage<R, MB, INV, WIDE>(buf, nrows, rowstride, d.n, Ns, d.radix[0], d.div_nb[s], d.div_ns[s], t, tid, nthr)
 template <bool ONE, bool INV, bool WIDE = false>
 __device__ __forceinline__ void fft_rows(float2* buf, int nrows, int rowstride, const FftDesc& d,
                                          const float2* __restrict__ tw, int tid, int nthr) {

@@ -528,14 +528,18 @@ int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride) {
   return 0;
 }
 
-// Whether a length takes its wide plan: if the widest tile it allows still has
-// a thread for every butterfly (the other plan runs two per thread instead of
-// narrowing the tile).
-bool lateral_wide(int L, int min_radix) {
-  const int rs = (L % 2 == 0) ? L + 1 : L;
-  int T = 32;
-  while (T > 1 && (int64_t)T * rs * 8 > 65280) T >>= 1;
-  return (int64_t)T * (L / min_radix) <= 1024;
+// Whether a line set takes the wide plan fd: if the widest tile still has a
+// thread for every butterfly (the radix-8 plan runs two per thread instead of
+// narrowing the tile), and its own tile has butterflies for three waves (with
+// fewer, as on small images, the long butterflies of one or two waves are the
+// pass: forward of 1750 x 128, 64 butterflies of radix 8 and 16, 24.5 us a
+// call against 23.8).
+bool lateral_wide(const LineGeom& lg, const FftDesc& fd) {
+  const int rs0 = (lg.L % 2 == 0) ? lg.L + 1 : lg.L;
+  int T = 32, rs = 0;
+  while (T > 1 && (int64_t)T * rs0 * 8 > 65280) T >>= 1;
+  if ((int64_t)T * (lg.L / fd.min_radix) > 1024) return false;
+  return (int64_t)lateral_pick_tile(lg, fd, &rs) * (lg.L / fd.min_radix) >= 192;
 }
 
 template <int MODE, int VAR, bool OFF32>
