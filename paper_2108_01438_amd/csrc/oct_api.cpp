@@ -48,7 +48,8 @@ double kb0(double u, int J, double b) {
   return (bessel_i0(b * std::sqrt(s)) - 1.0) / (bessel_i0(b) - 1.0);
 }
 
-double kb0_ft(double f, int J, double b) {
+// i0m1 = I0(b) - 1
+double kb0_ft(double f, int J, double b, double i0m1) {
   const double w = kPi * J * f;
   const double a2 = b * b - w * w;
   double sh;
@@ -62,7 +63,7 @@ double kb0_ft(double f, int J, double b) {
     sh = J;
   }
   const double box = (w == 0.0) ? (double)J : J * std::sin(w) / w;
-  return (sh - box) / (bessel_i0(b) - 1.0);
+  return (sh - box) / i0m1;
 }
 
 // Tap j of the J-tap window as a polynomial in x = 2 f - 1, f = frac(t):
@@ -1001,10 +1002,13 @@ oct_status oct_plan_create(const oct_geometry* g, const uint8_t* mask, oct_plan_
       beam[iy * p->Nx + ix] = g->beam_waist > 0 ? (float)std::exp(-qq * g->beam_waist * g->beam_waist / 8.0) : 1.f;
     }
   }
+  std::vector<double> deapd(p->Nz);
   std::vector<float> deap(p->Nz);
+  const double i0m1 = bessel_i0(p->kbb) - 1.0;
   for (int64_t n = 0; n < p->Nz; ++n) {
     const double f = (double)(n - p->nc) / (double)p->K;
-    deap[n] = (float)(1.0 / kb0_ft(f, p->J, p->kbb));
+    deapd[n] = 1.0 / kb0_ft(f, p->J, p->kbb, i0m1);
+    deap[n] = (float)deapd[n];
   }
   std::vector<float> kbc;
   kb_pieces(p->J, p->kbb, kbc);
@@ -1113,8 +1117,7 @@ oct_status oct_plan_create(const oct_geometry* g, const uint8_t* mask, oct_plan_
       const size_t nt = twc.size();
       for (int64_t n = 0; n < p->Nz; ++n) {
         const double a = -kPi * (double)(n - p->nc) / (double)p->Nz;
-        const double d = 1.0 / kb0_ft((double)(n - p->nc) / (double)p->K, p->J, p->kbb);
-        twc.push_back(make_float2((float)(d * std::cos(a)), (float)(d * std::sin(a))));
+        twc.push_back(make_float2((float)(deapd[n] * std::cos(a)), (float)(deapd[n] * std::sin(a))));
       }
       // one upload: twiddle rows (16-byte rows first), deap_odd, spans
       twc.resize((twc.size() + 1) & ~(size_t)1);

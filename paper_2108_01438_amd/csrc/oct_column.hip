@@ -23,7 +23,7 @@
 // Bound by vector arithmetic: 17.7 k vector instructions per pair of 2048-point
 // columns at 0.77 of the issue rate (23.2 k at 0.69 in the pair kernel).  Both
 // directions in one launch, pair kernel -> here: 2048 x 256 x 256 1.90 -> 1.31
-// ms, 32 x 1024 x 512 311 -> 167 us, 1400 x 1120 79 -> 50 us, 512 x 64 15.2 ->
+// ms, 32 x 1024 x 512 311 -> 167 us, 1400 x 1120 74 -> 33 us, 512 x 64 15.2 ->
 // 9.5 us; the adjoint of 1024 x 112 x 112 145 -> 69 us, forward and adjoint of
 // 2048 x 1000 17.2 and 21.5 -> 16.5 and 15.8 us.
 #include "oct_fft.h"
@@ -54,6 +54,12 @@ __device__ __forceinline__ double col_sqrt(double arg) {   // arg > 0; relative 
 
 __device__ __forceinline__ int padk(int i) { return i + (i >> 4); }   // spreads strided LDS accesses over the banks
 
+// Runtime lengths: only a first stage whose radix is a multiple of 4 leaves the
+// padded layout (other strides meet at most two lanes in a bank); everything
+// else is natural, one addition per access instead of four operations.
+template <int R, int CN>
+__device__ __forceinline__ int col_first_w(int j, int r);
+
 // padk(base + r NS) for a stage's writes, with constant offsets where base's
 // low bits are known
 template <int R, int NS>
@@ -68,6 +74,12 @@ template <int NB>
 __device__ __forceinline__ int pad_r(int j, int r, int nb) {
   if constexpr (NB > 0 && NB % 16 == 0) return padk(j) + r * (NB + NB / 16);
   else return padk(j + r * nb);
+}
+
+template <int R, int CN>
+__device__ __forceinline__ int col_first_w(int j, int r) {   // where a first stage writes output r of butterfly j
+  if constexpr (CN != 0 || R % 4 == 0) return pad_w<R, 1>(j * R, r);
+  else return j * R + r;
 }
 
 template <int R, bool INV>
@@ -118,23 +130,24 @@ __device__ __forceinline__ void col_fwd_first(const ColArgs& a, const ColLds& l,
     Dft<R, false>::run(v);
     float2* dst = l.row(0, c);
 #pragma unroll
-    for (int r = 0; r < R; ++r) dst[2 * pad_w<R, 1>(j * R, r)] = v[r];
+    for (int r = 0; r < R; ++r) dst[2 * col_first_w<R, CN>(j, r)] = v[r];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = cmul(x[r], a.deap_odd[depth(r)]);
     Dft<R, false>::run(v);
     dst = l.row(1, c);
 #pragma unroll
-    for (int r = 0; r < R; ++r) dst[2 * pad_w<R, 1>(j * R, r)] = v[r];
+    for (int r = 0; r < R; ++r) dst[2 * col_first_w<R, CN>(j, r)] = v[r];
   }
   __syncthreads();
 }
 
 // A stage in place over the four rows, up to MB butterflies per thread.
-// NAT_IN / NAT_OUT: natural instead of padded layout; the last forward stage
-// (NAT_OUT) also writes the wrapped cells after each row.
-template <int R, int MB, int CN, int CNS, bool INV, bool NAT_IN, bool NAT_OUT>
+// FIRST: the inverse's first stage (natural input).  LAST: the forward's last
+// (natural output, and the wrapped cells after each row).  pin (runtime
+// lengths): the input is padded.
+template <int R, int MB, int CN, int CNS, bool INV, bool FIRST, bool LAST>
 __device__ __forceinline__ void col_stage(const ColLds& l, int n, int ns, const FastDiv& dns,
-                                          const float2* __restrict__ tw, int tid, int nthr) {
+                                          const float2* __restrict__ tw, bool pin, int tid, int nthr) {
   const int N = CN ? CN : n, Ns = CNS ? CNS : ns;
   const int nb = N / R;
   // opaque: the addresses of every radix in the stage loop's switch would
@@ -148,13 +161,19 @@ __device__ __forceinline__ void col_stage(const ColLds& l, int n, int ns, const 
     if (q < 2 * nb) {
       par[b] = q >= nb ? 1 : 0;
       const int j = q - par[b] * nb;
-      const int k = CNS ? j % CNS : j - (int)fdiv((uint32_t)j, dns) * Ns;
+      const int k = FIRST ? 0 : CNS ? j % CNS : j - (int)fdiv((uint32_t)j, dns) * Ns;
       const float2* src = l.row(par[b], c);
+      if (FIRST || (CN == 0 && !pin)) {
+        const float2* s = src + 2 * j;
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[b][r] = src[2 * (NAT_IN ? j + r * nb : pad_r<CN / R>(j, r, nb))];
-      if (CNS != 1 && Ns > 1) col_twiddle<R, INV>(v[b], tw, k);
+        for (int r = 0; r < R; ++r) v[b][r] = s[2 * r * nb];
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b][r] = src[2 * pad_r<CN / R>(j, r, nb)];
+      }
+      if (!FIRST) col_twiddle<R, INV>(v[b], tw, k);
       Dft<R, INV>::run(v[b]);
-      base[b] = (j - k) * R + k;
+      base[b] = FIRST ? j : (j - k) * R + k;
     }
   }
   __syncthreads();
@@ -163,16 +182,17 @@ __device__ __forceinline__ void col_stage(const ColLds& l, int n, int ns, const 
     const int c = (tid + b * nthr) & 1, q = (tid + b * nthr) >> 1;
     if (q < 2 * nb) {
       float2* dst = l.row(par[b], c);
-      if (NAT_OUT) {
+      if (FIRST) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) dst[2 * (base[b] + r * Ns)] = v[b][r];
-        if (base[b] < COL_PADK) dst[2 * (N + base[b])] = v[b][0];   // the last stage: base = k < Ns, Ns >= COL_PADK
+        for (int r = 0; r < R; ++r) dst[2 * col_first_w<R, CN>(base[b], r)] = v[b][r];
+      } else if (LAST || CN == 0) {
+        float2* d = dst + 2 * base[b];
+#pragma unroll
+        for (int r = 0; r < R; ++r) d[2 * r * Ns] = v[b][r];
+        if (LAST && base[b] < COL_PADK) dst[2 * (N + base[b])] = v[b][0];   // base = k < Ns, Ns >= COL_PADK
       } else {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int o = CNS ? pad_w<R, CNS>(base[b], r) : padk(base[b] + r * Ns);
-          dst[2 * o] = v[b][r];
-        }
+        for (int r = 0; r < R; ++r) dst[2 * pad_w<R, CNS>(base[b], r)] = v[b][r];
       }
     }
   }
@@ -182,7 +202,7 @@ __device__ __forceinline__ void col_stage(const ColLds& l, int n, int ns, const 
 // Last inverse stage: both rows of column c, joined and deapodised into memory.
 template <int R, int CN>
 __device__ __forceinline__ void col_inv_last(const ColArgs& a, const ColLds& l, const float2* __restrict__ tw,
-                                             float2* d0, float2* d1, int tid, int nthr) {
+                                             bool pin, float2* d0, float2* d1, int tid, int nthr) {
   const int N = CN ? CN : a.Nz, nc = CN ? CN / 2 : a.nc;
   const int nb = N / R;   // = Ns
   for (int item = tid; item < 2 * nb; item += nthr) {
@@ -191,11 +211,20 @@ __device__ __forceinline__ void col_inv_last(const ColArgs& a, const ColLds& l, 
     if (!dst) continue;
     float2 v[R], w[R];
     const float2 *ra = l.row(0, c), *rb = l.row(1, c);
+    if (CN == 0 && !pin) {
+      const float2 *sa = ra + 2 * j, *sb = rb + 2 * j;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int o = 2 * pad_r<CN / R>(j, r, nb);
-      v[r] = ra[o];
-      w[r] = rb[o];
+      for (int r = 0; r < R; ++r) {
+        v[r] = sa[2 * r * nb];
+        w[r] = sb[2 * r * nb];
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int o = 2 * pad_r<CN / R>(j, r, nb);
+        v[r] = ra[o];
+        w[r] = rb[o];
+      }
     }
     col_twiddle<R, true>(v, tw, j);
     Dft<R, true>::run(v);
@@ -250,21 +279,24 @@ __device__ __forceinline__ void col_forward(const ColArgs& a, const ColLds& l, c
   if constexpr (CN == 512 || CN == 1024 || CN == 2048) {
     constexpr int R1 = CN == 2048 ? 16 : 8, R2 = CN == 512 ? 8 : 16;
     col_fwd_first<8, CN>(a, l, s0, s1, tid, nthr);
-    col_stage<R1, MB, CN, 8, false, false, false>(l, CN, 8, none, a.tw + a.f.tw_off[1], tid, nthr);
-    col_stage<R2, MB, CN, 8 * R1, false, false, true>(l, CN, 8 * R1, none, a.tw + a.f.tw_off[2], tid, nthr);
+    col_stage<R1, MB, CN, 8, false, false, false>(l, CN, 8, none, a.tw + a.f.tw_off[1], true, tid, nthr);
+    col_stage<R2, MB, CN, 8 * R1, false, false, true>(l, CN, 8 * R1, none, a.tw + a.f.tw_off[2], true, tid, nthr);
   } else {
 #define COL_FIRST(R) col_fwd_first<R, 0>(a, l, s0, s1, tid, nthr)
     COL_EDGE_SWITCH(a.f.radix[0], COL_FIRST)
 #undef COL_FIRST
     const int last = a.f.ns - 1;
+    const bool pad = a.f.radix[0] % 4 == 0;
     for (int s = 1; s < last; ++s) {
 #define COL_MID(R) \
-  col_stage<R, MB, 0, 0, false, false, false>(l, a.Nz, a.f.sub[s], a.f.div_sub[s], a.tw + a.f.tw_off[s], tid, nthr)
+  col_stage<R, MB, 0, 0, false, false, false>(l, a.Nz, a.f.sub[s], a.f.div_sub[s], a.tw + a.f.tw_off[s], \
+                                              s == 1 && pad, tid, nthr)
       COL_RADIX_SWITCH(a.f.radix[s], COL_MID)
 #undef COL_MID
     }
 #define COL_LAST(R) \
-  col_stage<R, MB, 0, 0, false, false, true>(l, a.Nz, a.f.sub[last], a.f.div_sub[last], a.tw + a.f.tw_off[last], tid, nthr)
+  col_stage<R, MB, 0, 0, false, false, true>(l, a.Nz, a.f.sub[last], a.f.div_sub[last], a.tw + a.f.tw_off[last], \
+                                             last == 1 && pad, tid, nthr)
     COL_RADIX_SWITCH(a.f.radix[last], COL_LAST)
 #undef COL_LAST
   }
@@ -276,22 +308,24 @@ __device__ __forceinline__ void col_inverse(const ColArgs& a, const ColLds& l, f
   const FastDiv none{};
   if constexpr (CN == 512 || CN == 1024 || CN == 2048) {
     constexpr int R0 = CN == 512 ? 8 : 16, R1 = CN == 2048 ? 16 : 8;
-    col_stage<R0, MB, CN, 1, true, true, false>(l, CN, 1, none, a.tw, tid, nthr);
-    col_stage<R1, MB, CN, R0, true, false, false>(l, CN, R0, none, a.tw + a.i.tw_off[1], tid, nthr);
-    col_inv_last<8, CN>(a, l, a.tw + a.i.tw_off[2], d0, d1, tid, nthr);
+    col_stage<R0, MB, CN, 1, true, true, false>(l, CN, 1, none, a.tw, false, tid, nthr);
+    col_stage<R1, MB, CN, R0, true, false, false>(l, CN, R0, none, a.tw + a.i.tw_off[1], true, tid, nthr);
+    col_inv_last<8, CN>(a, l, a.tw + a.i.tw_off[2], true, d0, d1, tid, nthr);
   } else {
     const FastDiv one = a.i.div_sub[0];
-#define COL_FIRST(R) col_stage<R, MB, 0, 0, true, true, false>(l, a.Nz, 1, one, a.tw, tid, nthr)
+#define COL_FIRST(R) col_stage<R, MB, 0, 0, true, true, false>(l, a.Nz, 1, one, a.tw, false, tid, nthr)
     COL_RADIX_SWITCH(a.i.radix[0], COL_FIRST)
 #undef COL_FIRST
     const int last = a.i.ns - 1;
+    const bool pad = a.i.radix[0] % 4 == 0;
     for (int s = 1; s < last; ++s) {
 #define COL_MID(R) \
-  col_stage<R, MB, 0, 0, true, false, false>(l, a.Nz, a.i.sub[s], a.i.div_sub[s], a.tw + a.i.tw_off[s], tid, nthr)
+  col_stage<R, MB, 0, 0, true, false, false>(l, a.Nz, a.i.sub[s], a.i.div_sub[s], a.tw + a.i.tw_off[s], \
+                                             s == 1 && pad, tid, nthr)
       COL_RADIX_SWITCH(a.i.radix[s], COL_MID)
 #undef COL_MID
     }
-#define COL_LAST(R) col_inv_last<R, 0>(a, l, a.tw + a.i.tw_off[last], d0, d1, tid, nthr)
+#define COL_LAST(R) col_inv_last<R, 0>(a, l, a.tw + a.i.tw_off[last], last == 1 && pad, d0, d1, tid, nthr)
     COL_EDGE_SWITCH(a.i.radix[last], COL_LAST)
 #undef COL_LAST
   }
@@ -654,7 +688,7 @@ hipError_t col_launch(const ColArgs& a, const float2* X, float2* W, const PairRe
     case 512: return COL_T(6, 512, 5, 2);
     case 1024: return COL_T(6, 1024, 5, 2);
     case 2048: return COL_T(6, 2048, 5, 1);
-    default: return COL_T(6, 0, 5, 2);
+    default: return spt == 3 ? COL_T(6, 0, 3, 2) : COL_T(6, 0, 5, 2);
   }
 #undef COL_T
 }
@@ -683,18 +717,34 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 // and more pairs share a CU.  Launches of at most eight waves a CU, where a
 // pair's chain is what counts, take two cells and one butterfly (forward of
 // 245 x 600, 301 pairs: 22.2 us a call against 24.4).
+//
+// A CU holds 16 waves of these kernels, and a workgroup's waves go to its four
+// SIMDs in turn, so one of five waves takes the room of eight (1400 x 1120: 561
+// pairs in two rounds of 512).  Where three cells per thread fill more of it
+// than five they are taken (with the natural layout, both directions of 1400 x
+// 1120 50 -> 33 us).
 int col_threads(const ColArgs& a, int* spt, int* mb) {
   int items = 0;
   for (int s = 1; s < a.f.ns; ++s) items = std::max(items, 4 * (a.Nz / a.f.radix[s]));
   const int64_t pairs = (int64_t)a.n_pairs * a.batch;
-  for (int c : {2, 5}) {
-    if (c == 2 && a.J != 6) continue;
-    *spt = c;
-    *mb = c == 2 || a.Nz == 2048 ? 1 : 2;
-    const int nt = (std::max((items + *mb - 1) / *mb, (a.span + a.J - 1 + c - 1) / c) + 63) & ~63;
-    if (nt <= 1024 && (c != 2 || pairs * (nt / 64) <= 8 * 256)) return nt;
+  auto threads = [&](int c, int m) {
+    return (std::max((items + m - 1) / m, (a.span + a.J - 1 + c - 1) / c) + 63) & ~63;
+  };
+  *mb = 1;
+  *spt = 2;
+  int nt = threads(2, 1);
+  if (a.J == 6 && nt <= 1024 && pairs * (nt / 64) <= 8 * 256) return nt;
+  *mb = a.Nz == 2048 ? 1 : 2;
+  *spt = 5;
+  nt = threads(5, *mb);
+  if (a.J == 6 && a.Nz != 512 && a.Nz != 1024 && a.Nz != 2048) {
+    auto resident = [](int t) { return t > 1024 ? 0 : 16 / ((t / 64 + 3) & ~3) * (t / 64); };
+    if (resident(threads(3, 2)) > resident(nt)) {
+      *spt = 3;
+      nt = threads(3, 2);
+    }
   }
-  return 0;
+  return nt <= 1024 ? nt : 0;
 }
 
 // K = 2 N with a transform plan, samples at least one cell apart (spacing
