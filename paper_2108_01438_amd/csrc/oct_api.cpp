@@ -876,12 +876,10 @@ oct_status run_prox(oct_plan* p, int pen, float tau, float bound, int tv_inner, 
     if (bound < INFINITY) return fail(OCT_E_UNSUPPORTED, "a modulus bound with the DT-CWT step has no closed form");
     OCTCHK(check_dtcwt(p, haar_levels));
     HIPCHK(launch_prox_dtcwt(pg, haar_levels, v, z, tau, p->dtwork, s));
-    *np = 1;
+    *np = 0;   // without a value pass there are no partials (and nothing reads them)
     if (want_value) {
       HIPCHK(launch_dtcwt_value(pg, haar_levels, z, p->dtwork, p->partial, s));
       *np = dtcwt_partials(pg, haar_levels);
-    } else {
-      HIPCHK(launch_zero(reinterpret_cast<float2*>(p->partial), 1, s));
     }
   } else {
     return fail(OCT_E_INVALID, "unknown penalty");

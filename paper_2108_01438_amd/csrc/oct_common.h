@@ -309,8 +309,8 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
                           float bound, double* partial, float2* work, float2* img_scratch, hipStream_t s);
 size_t tv_work_elems(const ProxGeom& g);
 // DT-CWT: z = W^T soft_tau(W v); work holds dtcwt_work_elems complex values
-// (B-scan: four trees and four staging arrays; volume: eight trees and sixteen
-// staging arrays); the value pass writes sum |W x| over the detail bands as
+// (B-scan: the bands of four trees twice, used by alternate levels; volume:
+// eight trees and sixteen staging arrays); the value pass writes sum |W x| over the detail bands as
 // dtcwt_partials block partials.
 int dtcwt_partials(const ProxGeom& g, int levels);
 size_t dtcwt_work_elems(const ProxGeom& g);

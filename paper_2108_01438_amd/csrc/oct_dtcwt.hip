@@ -11,9 +11,9 @@
 // for tree b; later levels: the 12-tap pair (K = 3, L = 3).
 //
 // Transform: four separable orthonormal 2-D DWTs (depth filters of tree a
-// or b x lateral filters of tree a or b), periodic extension, per level a
-// depth pass then a lateral pass, bands kept in place (Mallat layout) in one
-// buffer per tree.  The detail bands of the four trees combine per element
+// or b x lateral filters of tree a or b), periodic extension, both axes and
+// all four trees of a level in one pass, bands in Mallat layout in one buffer
+// per tree.  The detail bands of the four trees combine per element
 // into the six oriented complex subbands (u1, v1) = (aa - bb, ab + ba)/sqrt2,
 // (u2, v2) = (aa + bb, ab - ba)/sqrt2.  With the 1/2 scaling of the trees the
 // transform W is a Parseval frame; the shrinkage step W^T soft_tau(W v) is
@@ -33,28 +33,12 @@ struct DtFilt {
   int n;
 };
 
-struct DtGeom {
-  int B, NX, NZ;      // image [B][NX][NZ]
-  int nx, nz;         // current (sub-)array at the top-left of every item
-};
-
 // Periodic one-level filter banks along one axis of the top-left nx x nz
 // sub-array of every image of the batch.  Analysis: lo[i] = sum_k h0[k]
 // x[(2i + k) mod n], hi[i] likewise with h1, lo to the first half of the
 // axis and hi to the second.  Synthesis is its transpose (the analysis is
 // orthogonal): x[m] = sum over k with m - k even of h0[k] lo[i] + h1[k] hi[i],
-// i = ((m - k) mod n) / 2.  blockIdx.y selects one of up to four (source,
-// filter, destination) jobs of a launch (the four trees, or the two depth
-// filters of the first level); ACC makes a synthesis job add the output of
-// job y + 1 (same destination), so two trees that share the next pass are
-// summed on the way.
-
-struct DtJobs {
-  const float2* src[4];
-  float2* dst[4];
-  DtFilt f[4];
-  float scale;      // applied to synthesis outputs
-};
+// i = ((m - k) mod n) / 2.
 
 __device__ __forceinline__ void fma2(float2& acc, float w, float2 x) {
   acc.x = fmaf(w, x.x, acc.x);
@@ -88,47 +72,6 @@ __device__ __forceinline__ float2 sfb_line(const DtFilt& f, const float2* __rest
   return x;
 }
 
-// depth analysis: thread = (batch, lateral l < nx, i < nz/2), i fastest
-__global__ void afb_depth_kernel(DtGeom g, DtJobs J) {
-  const int j = blockIdx.y;
-  const int h = g.nz / 2;
-  const int64_t total = (int64_t)g.B * g.nx * h;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(t % h);
-    const int64_t r = t / h;
-    const int l = (int)(r % g.nx);
-    const int b = (int)(r / g.nx);
-    const int64_t base = ((int64_t)b * g.NX + l) * g.NZ;
-    float2 lo, hi;
-    afb_line(J.f[j], J.src[j] + base, 1, g.nz, i, lo, hi);
-    J.dst[j][base + i] = lo;
-    J.dst[j][base + h + i] = hi;
-  }
-}
-
-template <bool ACC>
-__global__ void sfb_depth_kernel(DtGeom g, DtJobs J) {
-  const int j = blockIdx.y * (ACC ? 2 : 1);
-  const int64_t total = (int64_t)g.B * g.nx * g.nz;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int m = (int)(t % g.nz);
-    const int64_t r = t / g.nz;
-    const int l = (int)(r % g.nx);
-    const int b = (int)(r / g.nx);
-    const int64_t base = ((int64_t)b * g.NX + l) * g.NZ;
-    float2 x = sfb_line(J.f[j], J.src[j] + base, 1, g.nz, m);
-    if (ACC) {
-      const float2 y = sfb_line(J.f[j + 1], J.src[j + 1] + base, 1, g.nz, m);
-      x = make_float2(x.x + y.x, x.y + y.y);
-    }
-    J.dst[j][base + m] = make_float2(J.scale * x.x, J.scale * x.y);
-  }
-}
-
-struct Trees {
-  float2* t[4];   // trees aa, ab, ba, bb
-};
-
 __device__ __forceinline__ float2 add2(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 sub2(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 
@@ -159,60 +102,149 @@ __device__ __forceinline__ void dt_group(float2 (&w)[4], float tau2, double& acc
   w[2] = cscale(sub2(v1, v2), r2);
 }
 
-// LDS-tiled lateral synthesis.  A workgroup (4 waves) owns 64 consecutive
-// depth samples (one per lane) and a run of lateral output rows; it stages
-// the input rows those outputs need (periodic wrap resolved while staging) in
-// LDS once, so that every tap is an LDS read instead of a strided global one.
-// (The analysis stays untiled: measured faster, its taps hit the caches.)
-constexpr int DT_LANES = 64;
-
 // Threads a register-window pass needs before it replaces the per-tap kernel
 // (about four workgroups per CU): below that the walk along the axis leaves
 // too few threads, and the per-tap kernel's rows fit the caches anyway.
 constexpr int64_t DT_WINDOW_MIN_THREADS = (int64_t)1 << 18;
 
-__device__ __forceinline__ void dt_stage(const float2* __restrict__ src, int64_t item, int NZ, int n, int base,
-                                         int nrows, int n0, int nz, int rowoff, float2* __restrict__ lds) {
-  for (int e = threadIdx.x; e < nrows * DT_LANES; e += blockDim.x) {
-    const int r = e / DT_LANES, c = e % DT_LANES;
-    int m = (base + r) % n;
-    if (m < 0) m += n;
-    const int nn = n0 + c;
-    lds[e] = nn < nz ? src[item + (int64_t)(rowoff + m) * NZ + nn] : make_float2(0.f, 0.f);
-  }
-}
+// One level of a B-scan's four trees (tree 2 d + l: depth filter d, lateral
+// filter l; 0 = a, 1 = b).  nx x nz is the sub-array at the top-left of every
+// item that the level splits (analysis) or rebuilds (synthesis).
+struct DtLevel {
+  int B, NX, NZ, nx, nz;
+  const float2* src;   // tree t at src + t * sstride
+  float2* dst;         // tree t at dst + t * dstride
+  int64_t sstride, dstride;
+  float f[2][2][12];   // [filter a, b][h0, h1][tap]
+};
 
-// Lateral analysis of all four trees at once (thread = (batch, i < nx/2,
-// depth n < nz)), with the detail bands of the level handled on the spot:
-// lateral-low outputs in the depth-low half are the next level's low band
-// and are written as they are; every other output is a detail coefficient,
-// combined across the trees and shrunk (SHRINK, then written) or summed into
-// FP64 block partials (value pass: only the low band is written).
-template <bool SHRINK>
-__global__ void afb_lateral4_kernel(DtGeom g, DtJobs J, float tau2, double* partial) {
-  __shared__ double sh[16];
-  const int h = g.nx / 2, hz = g.nz / 2;
-  const int64_t total = (int64_t)g.B * h * g.nz;
+// One analysis level, both axes and all four trees in one pass.  Four separate
+// lateral and depth passes moved every tree through memory twice per level with
+// one load per tap.  A workgroup owns DZ depth x P G lateral outputs of every
+// band: each thread walks 2 P + NT - 2 rows of one depth column (all loads
+// independent, coalesced along depth; every row of a column is loaded once per
+// P outputs) and leaves the lateral bands in LDS; the depth filters then run
+// along LDS rows by 16-byte reads, and one thread holds all four trees of a
+// position, as the shrinkage of the details needs.  Lateral-low depth-low
+// outputs are the next level's low band and are written as they are; every
+// other output is a detail coefficient, combined across the trees and shrunk
+// (SHRINK, then written) or summed into an FP64 block partial (value pass: only
+// the low band is written).  NS = 1: the first level, where the trees share one
+// source; NS = 4: a source per tree.  Sources and destinations are different
+// buffers (workgroups read their neighbours' rows).
+// Bound: 16 MB in and 66 MB out at the first level of a 2048 x 1000 B-scan
+// (17 us at the copy rate); measured 18.1 us there and 11.5 + 7.4 at the next
+// two levels, 37 in all, where the separate depth and lateral passes took 95.
+template <bool SHRINK, int NT, int NS, int DZ, int P, int G, int THREADS>
+__global__ void __launch_bounds__(THREADS) dt_analysis_kernel(DtLevel a, float tau2, double* partial) {
+  constexpr int RX = P * G, PW = 2 * DZ + NT - 2, NA = NS == 1 ? 2 : 4;
+  static_assert(PW % 2 == 0, "16-byte LDS rows");
+  __shared__ __align__(16) float2 band[NA][2][RX][PW];
+  const int h = a.nx / 2, hz = a.nz / 2;
+  const int tz = (hz + DZ - 1) / DZ, tx = (h + RX - 1) / RX;
+  const int64_t tiles = (int64_t)a.B * tx * tz;
   double acc = 0.0;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int n = (int)(t % g.nz);
-    const int64_t r = t / g.nz;
-    const int i = (int)(r % h);
-    const int b = (int)(r / h);
-    const int64_t item = (int64_t)b * g.NX * g.NZ + n;
-    float2 lo[4], hi[4];
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int i0 = (int)(tile % tz) * DZ, r0 = (int)(tile / tz % tx) * RX;
+    const int64_t item = tile / tz / tx * a.NX * a.NZ;
+    if (tile != blockIdx.x) __syncthreads();
+    for (int e = threadIdx.x; e < NS * G * PW; e += THREADS) {
+      const int c = e % PW, g = e / PW % G, t = e / PW / G;
+      const int r = r0 + g * P;
+      if (r >= h) continue;
+      const float2* p = a.src + t * a.sstride + item + (int64_t)(2 * r) * a.NZ + (2 * i0 + c) % a.nz;
+      float2 x[2 * P + NT - 2];
+      int m = 2 * r;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) afb_line(J.f[k], J.src[k] + item, g.NZ, g.nx, i, lo[k], hi[k]);
-    const int64_t olo = item + (int64_t)i * g.NZ, ohi = item + (int64_t)(h + i) * g.NZ;
-    if (n >= hz) dt_group<SHRINK>(lo, tau2, acc);
-    dt_group<SHRINK>(hi, tau2, acc);
+      for (int u = 0; u < 2 * P + NT - 2; ++u) {
+        x[u] = *p;
+        p += a.NZ;
+        if (++m == a.nx) {
+          m = 0;
+          p -= (int64_t)a.nx * a.NZ;
+        }
+      }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (SHRINK || n < hz) J.dst[k][olo] = lo[k];
-      if (SHRINK) J.dst[k][ohi] = hi[k];
+      for (int l = 0; l < (NS == 1 ? 2 : 1); ++l) {
+        const bool fb = NS == 1 ? l == 1 : (t & 1) == 1;
+        float2 lo[P], hi[P];
+#pragma unroll
+        for (int o = 0; o < P; ++o) lo[o] = hi[o] = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          const float w0 = fb ? a.f[1][0][k] : a.f[0][0][k];
+          const float w1 = fb ? a.f[1][1][k] : a.f[0][1][k];
+#pragma unroll
+          for (int o = 0; o < P; ++o) {
+            fma2(lo[o], w0, x[2 * o + k]);
+            fma2(hi[o], w1, x[2 * o + k]);
+          }
+        }
+        const int arr = NS == 1 ? l : t;
+#pragma unroll
+        for (int o = 0; o < P; ++o) {
+          band[arr][0][g * P + o][c] = lo[o];
+          band[arr][1][g * P + o][c] = hi[o];
+        }
+      }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < RX * DZ; e += THREADS) {
+      const int c = e % DZ, row = e / DZ;
+      const int i = i0 + c, r = r0 + row;
+      if (i >= hz || r >= h) continue;
+      float2 ll[4], lh[4], hl[4], hh[4];   // [lateral band][depth band]
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+#pragma unroll
+        for (int lat = 0; lat < 2; ++lat) {
+          float2 x[NT];
+          const float4* row4 = reinterpret_cast<const float4*>(&band[q][lat][row][2 * c]);
+#pragma unroll
+          for (int k = 0; k < NT / 2; ++k) {
+            const float4 v = row4[k];
+            x[2 * k] = make_float2(v.x, v.y);
+            x[2 * k + 1] = make_float2(v.z, v.w);
+          }
+#pragma unroll
+          for (int s = 0; s < (NS == 1 ? 2 : 1); ++s) {
+            const int t = NS == 1 ? 2 * s + q : q, d = t >> 1;
+            float2 lo = make_float2(0.f, 0.f), hi = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int k = 0; k < NT; ++k) {
+              fma2(lo, a.f[d][0][k], x[k]);
+              fma2(hi, a.f[d][1][k], x[k]);
+            }
+            // one LDS row's taps at a time: with all in flight the registers leave one workgroup per CU
+            asm volatile("" : "+v"(lo.x), "+v"(lo.y), "+v"(hi.x), "+v"(hi.y)::"memory");
+            if (lat == 0) {
+              ll[t] = lo;
+              lh[t] = hi;
+            } else {
+              hl[t] = lo;
+              hh[t] = hi;
+            }
+          }
+        }
+      }
+      dt_group<SHRINK>(lh, tau2, acc);
+      dt_group<SHRINK>(hl, tau2, acc);
+      dt_group<SHRINK>(hh, tau2, acc);
+      float2* olo = a.dst + item + (int64_t)r * a.NZ + i;
+      float2* ohi = olo + (int64_t)h * a.NZ;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        olo[t * a.dstride] = ll[t];
+        if (SHRINK) {
+          olo[t * a.dstride + hz] = lh[t];
+          ohi[t * a.dstride] = hl[t];
+          ohi[t * a.dstride + hz] = hh[t];
+        }
+      }
     }
   }
   if (!SHRINK) {
+    __shared__ double sh[THREADS / 64];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -220,53 +252,109 @@ __global__ void afb_lateral4_kernel(DtGeom g, DtJobs J, float tau2, double* part
     __syncthreads();
     if (threadIdx.x == 0) {
       double s = 0.0;
-      for (int k = 0; k < (int)(blockDim.x >> 6); ++k) s += sh[k];
+      for (int k = 0; k < THREADS / 64; ++k) s += sh[k];
       partial[blockIdx.x] = s;
     }
   }
 }
 
-// Lateral synthesis (the transpose of the analysis along the lateral axis):
-// TS output rows per workgroup; blockIdx.y picks the job (ACC: the job pair
-// summed into one destination).
-template <bool ACC>
-__global__ void __launch_bounds__(256) sfb_lateral_tiled(DtGeom g, DtJobs J) {
-  constexpr int TS = 32;
-  constexpr int NS = ACC ? 2 : 1;
-  constexpr int CNT = (TS + DT_MAXT) / 2 + 1;
-  __shared__ float2 lo_s[NS][CNT * DT_LANES], hi_s[NS][CNT * DT_LANES];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * DT_LANES, m0 = blockIdx.z * TS;
-  const int j = blockIdx.y * NS;
-  const int h = g.nx / 2;
-  const int B = g.B;
-  for (int b = 0; b < B; ++b) {
-    const int64_t item = (int64_t)b * g.NX * g.NZ;
-    const int taps = NS == 2 ? max(J.f[j].n, J.f[j + 1].n) : J.f[j].n;   // rows staged for every job
-    const int ibase = (m0 - taps + 1) >> 1;
-    const int cnt = (m0 + TS - 1 - ((m0 - taps + 1) & ~1)) / 2 + 1;
-    if (b > 0) __syncthreads();
+// One synthesis level (the transpose of the analysis), both axes in one pass.
+// A workgroup owns 2 DZ depth x 2 P G lateral outputs.  Outputs 2p and 2p + 1
+// read the same NT / 2 rows p - NT / 2 + 1 .. p of each band, so a thread takes
+// P row pairs of one depth column of one depth band (P + NT / 2 - 1 rows of
+// both lateral bands, all loads independent) and leaves the laterally
+// synthesised column in LDS; the depth synthesis reads it there, each thread
+// with the taps of its own parity, and writes along depth.  ND = 2: the first
+// level, the four trees summed into dst (both lateral trees of a depth filter
+// before LDS) and scaled; ND = 1: one tree per blockIdx.y.  Sources and
+// destinations are different buffers.
+// Bound: 66 MB in and 16 MB out at the first level of a 2048 x 1000 B-scan
+// (17 us at the copy rate); measured 21.7 us there and 16.8 for the two levels
+// below, 38 in all, where the separate lateral and depth passes took 124.
+template <int NT, int ND, int DZ, int P, int G, int THREADS>
+__global__ void __launch_bounds__(THREADS) dt_synthesis_kernel(DtLevel a, float scale) {
+  constexpr int W = NT / 2, RX = P * G, CW = DZ + W - 1;
+  static_assert(THREADS % 2 == 0, "a thread keeps its parity");
+  __shared__ float2 mid[ND][2 * RX][2 * CW];
+  const int h = a.nx / 2, hz = a.nz / 2;
+  const int tz = (hz + DZ - 1) / DZ, tx = (h + RX - 1) / RX;
+  const int64_t tiles = (int64_t)a.B * tx * tz;
+  const int tree = blockIdx.y;
+  const int par = threadIdx.x & 1;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int i0 = (int)(tile % tz) * DZ, r0 = (int)(tile / tz % tx) * RX;
+    const int64_t item = tile / tz / tx * a.NX * a.NZ;
+    if (tile != blockIdx.x) __syncthreads();
+    for (int e = threadIdx.x; e < ND * G * 2 * CW; e += THREADS) {
+      const int c = e % (2 * CW), g = e / (2 * CW) % G, d = e / (2 * CW) / G;
+      const int p0 = r0 + g * P;
+      if (p0 >= h) continue;
+      int i = (i0 - (W - 1) + (c >= CW ? c - CW : c)) % hz;
+      if (i < 0) i += hz;
+      int m = (p0 - (W - 1)) % h;
+      if (m < 0) m += h;
+      const int64_t off = item + (int64_t)m * a.NZ + (c >= CW ? hz + i : i);
+      float2 x[2 * P];
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-      dt_stage(J.src[j + q], item, g.NZ, h, ibase, cnt, n0, g.nz, 0, lo_s[q]);
-      dt_stage(J.src[j + q], item, g.NZ, h, ibase, cnt, n0, g.nz, h, hi_s[q]);
-    }
-    __syncthreads();
-    const int n = n0 + lane;
-    for (int r = 0; r < TS / 4; ++r) {
-      const int m = m0 + w * (TS / 4) + r;
-      if (m >= g.nx || n >= g.nz) continue;
-      float2 x = make_float2(0.f, 0.f);
+      for (int o = 0; o < 2 * P; ++o) x[o] = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int q = 0; q < NS; ++q) {
-        const DtFilt& f = J.f[j + q];
-        for (int t = m & 1; t < f.n; t += 2) {
-          const int row = ((m - t) >> 1) - ibase;
-          fma2(x, f.h0[t], lo_s[q][row * DT_LANES + lane]);
-          fma2(x, f.h1[t], hi_s[q][row * DT_LANES + lane]);
+      for (int l = 0; l < ND; ++l) {
+        const int t = ND == 2 ? 2 * d + l : tree;
+        const float* f0 = ND == 2 ? a.f[l][0] : a.f[tree & 1][0];
+        const float* f1 = ND == 2 ? a.f[l][1] : a.f[tree & 1][1];
+        const float2* p = a.src + t * a.sstride + off;
+        float2 lo[P + W - 1], hi[P + W - 1];
+        int mm = m;
+#pragma unroll
+        for (int u = 0; u < P + W - 1; ++u) {
+          lo[u] = *p;
+          hi[u] = p[(int64_t)h * a.NZ];
+          p += a.NZ;
+          if (++mm == h) {
+            mm = 0;
+            p -= (int64_t)h * a.NZ;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+#pragma unroll
+          for (int o = 0; o < P; ++o) {
+            fma2(x[2 * o + (k & 1)], f0[k], lo[o + W - 1 - (k >> 1)]);
+            fma2(x[2 * o + (k & 1)], f1[k], hi[o + W - 1 - (k >> 1)]);
+          }
         }
       }
-      J.dst[j][item + (int64_t)m * g.NZ + n] = make_float2(J.scale * x.x, J.scale * x.y);
+#pragma unroll
+      for (int o = 0; o < 2 * P; ++o) mid[d][2 * g * P + o][c] = x[o];
+    }
+    __syncthreads();
+    float w0[ND][W], w1[ND][W];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      const int fd = ND == 2 ? d : tree >> 1;
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        w0[d][k] = par ? a.f[fd][0][2 * k + 1] : a.f[fd][0][2 * k];
+        w1[d][k] = par ? a.f[fd][1][2 * k + 1] : a.f[fd][1][2 * k];
+      }
+    }
+    for (int e = threadIdx.x; e < 2 * RX * 2 * DZ; e += THREADS) {
+      const int c = e % (2 * DZ), row = e / (2 * DZ);
+      const int n = 2 * i0 + c, r = 2 * r0 + row;
+      if (n >= a.nz || r >= a.nx) continue;
+      float2 v = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int d = 0; d < ND; ++d) {
+        const float2* q = &mid[d][row][(c >> 1) + W - 1];
+        float2 x = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          fma2(x, w0[d][k], q[-k]);
+          fma2(x, w1[d][k], q[CW - k]);
+        }
+        v = d == 0 ? x : make_float2(v.x + x.x, v.y + x.y);
+      }
+      a.dst[tree * a.dstride + item + (int64_t)r * a.NZ + n] = make_float2(scale * v.x, scale * v.y);
     }
   }
 }
@@ -434,21 +522,6 @@ const DtFilters& filters() {
   return F;
 }
 
-// Workspace: four tree buffers then four staging buffers, one image each.
-struct DtWork {
-  Trees tr;
-  float2* tmp[4];
-};
-
-DtWork dt_work(float2* work, int64_t n) {
-  DtWork w;
-  for (int t = 0; t < 4; ++t) {
-    w.tr.t[t] = work + t * n;
-    w.tmp[t] = work + (4 + t) * n;
-  }
-  return w;
-}
-
 int dt_grid_y(int64_t n, int jobs) {
   int64_t b = (n + 255) / 256;
   const int64_t cap = 4096 / jobs;
@@ -456,62 +529,108 @@ int dt_grid_y(int64_t n, int jobs) {
   return (int)(b < 1 ? 1 : b);
 }
 
-// Workgroups of the tiled lateral synthesis (32 output rows each, the batch
-// looped inside).
-dim3 dt_sfb_grid(const DtGeom& g, int jobs) {
-  return dim3((unsigned)((g.nz + DT_LANES - 1) / DT_LANES), (unsigned)jobs, (unsigned)((g.nx + 31) / 32));
+// Tile shapes of a B-scan's levels: depth outputs per band, lateral outputs
+// (or output pairs) per thread, threads' groups along the lateral axis, threads.
+// Enough threads that the columns of a tile take one turn (NS G (2 DZ + NT - 2)
+// and 2 ND G (DZ + NT / 2 - 1)) and workgroups small enough to overlap one's
+// loads with another's filters.  Measured at 2048 x 1000 (us): first analysis
+// 18.1 (G = 4 18.7, DZ = 64 18.6, P = 8 20.6, 320 threads at G = 4 20.5);
+// levels 2 and 3 of the analysis 11.5 + 7.4 (P = 4 13.4 + 6.6, G = 2 13.0 +
+// 7.8); first synthesis 21.7 (DZ = 32 with G = 4 22.2, G = 2 23.6, P = 8 30.5);
+// later synthesis 10.5 + 6.3 (G = 2 12.0 + 5.6, P = 8 12.2 + 6.7).
+constexpr int DTA1_DZ = 32, DTA1_P = 4, DTA1_G = 2, DTA1_T = 256;
+constexpr int DTA2_DZ = 32, DTA2_P = 8, DTA2_G = 1, DTA2_T = 320;
+constexpr int DTS1_DZ = 64, DTS1_P = 4, DTS1_G = 2, DTS1_T = 256;
+constexpr int DTS2_DZ = 32, DTS2_P = 4, DTS2_G = 3, DTS2_T = 256;
+constexpr int DT_N1 = 8, DT_N2 = 12;   // taps of the first level's and the later levels' filters
+
+DtLevel dt_level(const ProxGeom& pg, int lev) {
+  const DtFilters& F = filters();
+  DtLevel a{};
+  a.B = pg.B;
+  a.NX = pg.Nx;
+  a.NZ = pg.Nz;
+  a.nx = pg.Nx >> lev;
+  a.nz = pg.Nz >> lev;
+  for (int t = 0; t < 2; ++t) {
+    const DtFilt& f = lev == 0 ? F.first[t] : F.later[t];
+    for (int k = 0; k < f.n; ++k) {
+      a.f[t][0][k] = f.h0[k];
+      a.f[t][1][k] = f.h1[k];
+    }
+  }
+  return a;
 }
 
-// Analysis of all trees (level by level) from v into the tree buffers.
-// Level 1: the two depth filters once each (v -> tmp[0], tmp[1]), then the
-// lateral filters of every tree from its depth tree's staging buffer.  Later
-// levels: each tree's low band through tmp[t].
-// mode 0: analysis with the detail bands shrunk by tau2 on the way; mode 1:
-// the value pass (block partials of sum |W x| into partial, nothing but the
-// low bands written).
-hipError_t dt_analysis(const DtGeom& g0, int levels, const float2* v, const DtWork& w, int mode, float tau2,
+unsigned dt_tiles(const DtLevel& a, int dz, int rx, int64_t cap) {
+  const int64_t n = (int64_t)a.B * ((a.nz / 2 + dz - 1) / dz) * ((a.nx / 2 + rx - 1) / rx);
+  return (unsigned)(n < cap ? n : cap);
+}
+
+unsigned dt_analysis_grid(const DtLevel& a, int lev) {
+  return lev == 0 ? dt_tiles(a, DTA1_DZ, DTA1_P * DTA1_G, 4096) : dt_tiles(a, DTA2_DZ, DTA2_P * DTA2_G, 4096);
+}
+
+// Level lev's bands live in the first four images of the workspace (lev even)
+// or in the last four (odd): a level reads the low bands of the one before from
+// the other half, so no workgroup overwrites what a neighbour still reads.
+float2* dt_bands(const ProxGeom& pg, float2* work, int lev) {
+  return work + (lev & 1) * 4 * ((int64_t)pg.B * pg.Nx * pg.Nz);
+}
+
+template <bool SHRINK>
+void dt_analysis_level(const DtLevel& a, int lev, float tau2, double* partial, hipStream_t s) {
+  const dim3 grid(dt_analysis_grid(a, lev));
+  if (lev == 0)
+    hipLaunchKernelGGL((dt_analysis_kernel<SHRINK, DT_N1, 1, DTA1_DZ, DTA1_P, DTA1_G, DTA1_T>), grid, dim3(DTA1_T), 0,
+                       s, a, tau2, partial);
+  else
+    hipLaunchKernelGGL((dt_analysis_kernel<SHRINK, DT_N2, 4, DTA2_DZ, DTA2_P, DTA2_G, DTA2_T>), grid, dim3(DTA2_T), 0,
+                       s, a, tau2, partial);
+}
+
+// Analysis of all trees, level by level.  mode 0: the detail bands shrunk by
+// tau2 on the way; mode 1: the value pass (block partials of sum |W x| into
+// partial, nothing but the low bands written).
+hipError_t dt_analysis(const ProxGeom& pg, int levels, const float2* v, float2* work, int mode, float tau2,
                        double* partial, hipStream_t s) {
-  const DtFilters& F = filters();
-  DtGeom g = g0;
+  const int64_t n = (int64_t)pg.B * pg.Nx * pg.Nz;
   for (int lev = 0; lev < levels; ++lev) {
-    const DtFilt* fs = lev == 0 ? F.first : F.later;
-    const int64_t nd = (int64_t)g.B * g.nx * (g.nz / 2), nl = (int64_t)g.B * (g.nx / 2) * g.nz;
-    DtJobs jd{}, jl{};
-    int ndj;
-    if (lev == 0) {
-      ndj = 2;
-      for (int p = 0; p < 2; ++p) {
-        jd.src[p] = v;
-        jd.dst[p] = w.tmp[p];
-        jd.f[p] = fs[p];
-      }
-    } else {
-      ndj = 4;
-      for (int t = 0; t < 4; ++t) {
-        jd.src[t] = w.tr.t[t];
-        jd.dst[t] = w.tmp[t];
-        jd.f[t] = fs[t >> 1];
-      }
-    }
-    for (int t = 0; t < 4; ++t) {
-      jl.src[t] = lev == 0 ? w.tmp[t >> 1] : w.tmp[t];
-      jl.dst[t] = w.tr.t[t];
-      jl.f[t] = fs[t & 1];
-    }
-    hipLaunchKernelGGL(afb_depth_kernel, dim3(dt_grid_y(nd, ndj), ndj), dim3(256), 0, s, g, jd);
+    DtLevel a = dt_level(pg, lev);
+    a.src = lev == 0 ? v : dt_bands(pg, work, lev - 1);
+    a.sstride = lev == 0 ? 0 : n;
+    a.dst = dt_bands(pg, work, lev);
+    a.dstride = n;
     if (mode == 0) {
-      hipLaunchKernelGGL((afb_lateral4_kernel<true>), dim3(dt_grid(nl)), dim3(256), 0, s, g, jl, tau2, nullptr);
+      dt_analysis_level<true>(a, lev, tau2, nullptr, s);
     } else {
-      hipLaunchKernelGGL((afb_lateral4_kernel<false>), dim3(dt_grid(nl)), dim3(256), 0, s, g, jl, 0.f, partial);
-      partial += dt_grid(nl);
+      dt_analysis_level<false>(a, lev, 0.f, partial, s);
+      partial += dt_analysis_grid(a, lev);
     }
-    g.nx /= 2;
-    g.nz /= 2;
   }
   return hipGetLastError();
 }
 
-
+// Synthesis, coarsest level first; the first level sums the trees into z.
+hipError_t dt_synthesis(const ProxGeom& pg, int levels, float2* z, float2* work, hipStream_t s) {
+  const int64_t n = (int64_t)pg.B * pg.Nx * pg.Nz;
+  for (int lev = levels - 1; lev >= 0; --lev) {
+    DtLevel a = dt_level(pg, lev);
+    a.src = dt_bands(pg, work, lev);
+    a.sstride = n;
+    if (lev == 0) {
+      a.dst = z;
+      hipLaunchKernelGGL((dt_synthesis_kernel<DT_N1, 2, DTS1_DZ, DTS1_P, DTS1_G, DTS1_T>),
+                         dim3(dt_tiles(a, DTS1_DZ, DTS1_P * DTS1_G, 4096)), dim3(DTS1_T), 0, s, a, 0.25f);
+    } else {
+      a.dst = dt_bands(pg, work, lev - 1);
+      a.dstride = n;
+      hipLaunchKernelGGL((dt_synthesis_kernel<DT_N2, 1, DTS2_DZ, DTS2_P, DTS2_G, DTS2_T>),
+                         dim3(dt_tiles(a, DTS2_DZ, DTS2_P * DTS2_G, 1024), 4), dim3(DTS2_T), 0, s, a, 1.f);
+    }
+  }
+  return hipGetLastError();
+}
 
 // ---------------------------------------------------------------------------
 // Volumes: eight trees (depth, x, y filter trees), a pass per axis and level.
@@ -1004,12 +1123,7 @@ int dtcwt_partials(const ProxGeom& pg, int levels) {
     }
     return n;
   }
-  DtGeom g{pg.B, pg.Nx, pg.Nz, pg.Nx, pg.Nz};
-  for (int lev = 0; lev < levels; ++lev) {
-    n += dt_grid((int64_t)g.B * (g.nx / 2) * g.nz);
-    g.nx /= 2;
-    g.nz /= 2;
-  }
+  for (int lev = 0; lev < levels; ++lev) n += (int)dt_analysis_grid(dt_level(pg, lev), lev);
   return n;
 }
 
@@ -1101,49 +1215,10 @@ hipError_t launch_prox_dtcwt3(const ProxGeom& pg, int levels, const float2* v, f
 hipError_t launch_prox_dtcwt(const ProxGeom& pg, int levels, const float2* v, float2* z, float tau, float2* work,
                              hipStream_t s) {
   if (pg.lateral_dims == 2) return launch_prox_dtcwt3(pg, levels, v, z, tau, work, s);
-  const int64_t n = (int64_t)pg.B * pg.Nx * pg.Nz;
-  const DtWork w = dt_work(work, n);
-  const DtGeom g0{pg.B, pg.Nx, pg.Nz, pg.Nx, pg.Nz};
-  hipError_t e = dt_analysis(g0, levels, v, w, 0, 2.f * tau, nullptr, s);
+  // unscaled trees: soft threshold 2 tau, synthesis sum scaled by 1/4
+  hipError_t e = dt_analysis(pg, levels, v, work, 0, 2.f * tau, nullptr, s);
   if (e != hipSuccess) return e;
-  // synthesis, coarsest level first; level 1 sums the two trees of each depth
-  // filter after their lateral passes and the two depth filters at the end,
-  // with the 1/4 of the Parseval normalisation
-  const DtFilters& F = filters();
-  for (int lev = levels - 1; lev >= 0; --lev) {
-    DtGeom gl = g0;
-    gl.nx = pg.Nx >> lev;
-    gl.nz = pg.Nz >> lev;
-    const DtFilt* fs = lev == 0 ? F.first : F.later;
-    const int64_t nn = (int64_t)gl.B * gl.nx * gl.nz;
-    DtJobs jl{}, jd{};
-    jl.scale = jd.scale = 1.f;
-    for (int t = 0; t < 4; ++t) {
-      jl.src[t] = w.tr.t[t];
-      jl.dst[t] = w.tmp[t];
-      jl.f[t] = fs[t & 1];
-    }
-    if (lev > 0) {
-      for (int t = 0; t < 4; ++t) {
-        jd.src[t] = w.tmp[t];
-        jd.dst[t] = w.tr.t[t];
-        jd.f[t] = fs[t >> 1];
-      }
-      hipLaunchKernelGGL((sfb_lateral_tiled<false>), dt_sfb_grid(gl, 4), dim3(256), 0, s, gl, jl);
-      hipLaunchKernelGGL((sfb_depth_kernel<false>), dim3(dt_grid_y(nn, 4), 4), dim3(256), 0, s, gl, jd);
-    } else {
-      // tmp[0] = lat(aa) + lat(ab), tmp[2] = lat(ba) + lat(bb)
-      hipLaunchKernelGGL((sfb_lateral_tiled<true>), dt_sfb_grid(gl, 2), dim3(256), 0, s, gl, jl);
-      jd.src[0] = w.tmp[0];
-      jd.src[1] = w.tmp[2];
-      jd.dst[0] = jd.dst[1] = z;
-      jd.f[0] = fs[0];
-      jd.f[1] = fs[1];
-      jd.scale = 0.25f;
-      hipLaunchKernelGGL((sfb_depth_kernel<true>), dim3(dt_grid_y(nn, 1), 1), dim3(256), 0, s, gl, jd);
-    }
-  }
-  return hipGetLastError();
+  return dt_synthesis(pg, levels, z, work, s);
 }
 
 hipError_t launch_dtcwt_value(const ProxGeom& pg, int levels, const float2* x, float2* work, double* partial,
@@ -1153,10 +1228,7 @@ hipError_t launch_dtcwt_value(const ProxGeom& pg, int levels, const float2* x, f
     const Dt3Geom g0{pg.B, pg.Ny, pg.Nx, pg.Nz, pg.Ny, pg.Nx, pg.Nz};
     return dt3_analysis(g0, levels, x, dt3_work(work, n), 1, 0.f, partial, s);
   }
-  const int64_t n = (int64_t)pg.B * pg.Nx * pg.Nz;
-  const DtWork w = dt_work(work, n);
-  const DtGeom g0{pg.B, pg.Nx, pg.Nz, pg.Nx, pg.Nz};
-  return dt_analysis(g0, levels, x, w, 1, 0.f, partial, s);
+  return dt_analysis(pg, levels, x, work, 1, 0.f, partial, s);
 }
 
 // Host copies of the designed filters (for the library's own checks).
