@@ -752,8 +752,7 @@ int partial_need(oct_plan* p) {
   need = std::max(need, lat_blocks(b));
   ProxGeom pg{(int)p->B, (int)p->Ny, (int)p->Nx, (int)p->Nz, p->lat_dims};
   for (int lv = 1; lv <= 5; ++lv) need = std::max(need, haar_partials(pg, lv));
-  need = std::max(need, tv_partials(pg, TV_MAX_TILED_INNER));
-  need = std::max(need, tv_partials(pg, TV_MAX_TILED_INNER + 1));
+  for (int n = 1; n <= TV_MAX_TILED_INNER + 1; ++n) need = std::max(need, tv_partials(pg, n));
   for (int lv = 1; lv <= (p->lat_dims == 1 ? 5 : 4); ++lv) need = std::max(need, dtcwt_partials(pg, lv));
   need = std::max(need, (int)(p->n_pairs * p->B));   // the residual partials of the spectral seam
   return need;

@@ -630,16 +630,23 @@ __global__ void tv_value_kernel(TvIdx d, const float2* __restrict__ z, double* p
 
 // ---------------------------------------------------------------------------
 // 2-D TV by FGP with every inner step of a tile on chip.  Lane = depth sample
-// (64 per wave, coalesced), each thread owns a strip of TV_S lateral samples
-// in registers, 16 waves side by side laterally: a 64 x (16 TV_S) loaded
-// tile.  Depth neighbours move by lane shuffles, lateral neighbours inside a
-// strip are registers and across strips go through LDS.  One inner step
-// reaches one sample further in every direction, so with a halo of
-// n_inner + 1 the dual is exact on the core grown by one sample, which is
-// what z = v + tau div p and TV(z) on the core need.
+// (64 per wave, coalesced), each thread owns a strip of S lateral samples in
+// registers, WAVES waves side by side laterally: a 64 x (WAVES S) loaded tile.
+// Depth neighbours move by lane shuffles, lateral neighbours inside a strip are
+// registers and across strips go through LDS.  One inner step reaches one
+// sample further in every direction: with a halo of n_inner + 1 below (which z
+// = v + tau div p reads) and n_inner above the dual is exact on the core; TV(z),
+// where it is wanted, takes one more above.
+// Bound: the vector units (1.7 us per step and 256 tiles of 64 x 128) and the
+// loads and stores (about 15 us per 256 such tiles), in series when one
+// workgroup fills a CU.  Two workgroups of eight waves per CU overlap them but
+// spend more on halos (core 43 x 51 of 64 x 72 at ten steps, 43 x 107 of 64 x
+// 128); strips of nine are the longest whose state and temporaries leave four
+// waves per SIMD without spills in the steps (ten: 58.6 us, eight: 62.1).  Ten
+// steps on 2048 x 1000: 62.8 -> 53.0 us; on 8 x 1024 x 512: 131 -> 112 us.
 // ---------------------------------------------------------------------------
-constexpr int TV_S = 8;
-constexpr int TV_WAVES = 16;
+constexpr int TV_S1 = 9, TV_W1 = 8;
+constexpr int TV_S2 = 8, TV_W2 = 16;
 
 // The dual is kept zero wherever its component has no forward edge (last
 // index along that axis, and every sample outside the image).  The step of
@@ -647,13 +654,13 @@ constexpr int TV_WAVES = 16;
 // no boundary tests: (div p)_i = p_i - p_{i-1} along each axis.
 // BOUND: the constrained FGP of Beck and Teboulle, the primal point projected
 // onto C = {|x_i| <= bound} in every step and at the end.
-template <bool BOUND>
-__global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
+template <int S, int WAVES, bool BOUND>
+__global__ void __launch_bounds__(WAVES * 64, 4) tv2d_tile_kernel(Tv2dArgs a) {
   // strip-edge exchange rows: wave w publishes its last column in xr[w + 1]
-  // and its first in xd[w]; xr[0] and xd[TV_WAVES] stay zero, so every read
+  // and its first in xd[w]; xr[0] and xd[WAVES] stay zero, so every read
   // is unconditional
-  __shared__ float2 xr[TV_WAVES + 1][64];
-  __shared__ float2 xd[TV_WAVES + 1][64];
+  __shared__ float2 xr[WAVES + 1][64];
+  __shared__ float2 xd[WAVES + 1][64];
   __shared__ double sh[16];
   // the wave index is uniform: strip positions and lateral edge weights stay in
   // scalar registers
@@ -670,7 +677,7 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
   const int Nz = a.Nz, Nx = a.Nx, H = a.H;
   const int cz0 = tz * a.CZ, cl0 = tl * a.CL;
   const int n = cz0 - H + lane;
-  const int l0 = cl0 - H + w * TV_S;
+  const int l0 = cl0 - H + w * S;
   const bool nin = (n >= 0 && n < Nz);
   const bool zedge = (n >= 0 && n < Nz - 1);
   const int64_t ib = (int64_t)b * Nx * Nz;
@@ -683,22 +690,22 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
     return cscale(x, sc);
   };
   if (w == 0) xr[0][lane] = make_float2(0.f, 0.f);
-  if (w == TV_WAVES - 1) xd[TV_WAVES][lane] = make_float2(0.f, 0.f);
+  if (w == WAVES - 1) xd[WAVES][lane] = make_float2(0.f, 0.f);
 
   // FGP state per pixel: the extrapolated dual r and the previous dual P,
   // kept pre-multiplied by the momentum of the step that consumes it, so that
   // r = (1 + mom_k) p_k - mom_k p_{k-1} is one fused multiply-add per
   // component (mom after the last step is 1: P ends as the plain dual).  P is
   // updated in place: each pixel reads its old P before writing the new one.
-  float2 v[TV_S], Pz[TV_S], Pl[TV_S], rz[TV_S], rl[TV_S];
-  float sl[TV_S];
+  float2 v[S], Pz[S], Pl[S], rz[S], rl[S];
+  uint32_t lfwd = 0;   // bit s: strip row s has a lateral forward edge
   const float mom0 = a.mom[0];
 #pragma unroll
-  for (int s = 0; s < TV_S; ++s) {
+  for (int s = 0; s < S; ++s) {
     const int l = l0 + s;
     const bool in = nin && l >= 0 && l < Nx;
     const bool ledge = l >= 0 && l < Nx - 1;
-    sl[s] = ledge ? step : 0.f;
+    lfwd |= ledge ? 1u << s : 0u;
     const int64_t idx = ib + (int64_t)l * Nz + n;
     v[s] = in ? a.v[idx] : make_float2(0.f, 0.f);
     rz[s] = (in && zedge && a.pin) ? a.pin[idx] : make_float2(0.f, 0.f);
@@ -706,14 +713,15 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
     Pz[s] = cscale(rz[s], mom0);
     Pl[s] = cscale(rl[s], mom0);
   }
-  for (int k = 0; k < a.n_inner; ++k) {
+  auto inner = [&](int k) __attribute__((always_inline)) {
+    asm volatile("" : "+s"(lfwd));   // weights chosen by the scalar unit in each step, not kept in S registers
     const float mom1 = 1.f + a.mom[k];
     const float mnext = a.mom[k + 1];
-    xr[w + 1][lane] = rl[TV_S - 1];
+    xr[w + 1][lane] = rl[S - 1];
     __syncthreads();
-    float2 d[TV_S];
+    float2 d[S];
 #pragma unroll
-    for (int s = 0; s < TV_S; ++s) {
+    for (int s = 0; s < S; ++s) {
       const float2 lp = (s > 0) ? rl[s - 1] : xr[w][lane];
       const float dx = (rz[s].x - lane_prev(rz[s].x)) + (rl[s].x - lp.x);
       const float dy = (rz[s].y - lane_prev(rz[s].y)) + (rl[s].y - lp.y);
@@ -722,11 +730,12 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
     xd[w][lane] = d[0];
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < TV_S; ++s) {
-      const float2 dl = (s < TV_S - 1) ? d[s + 1] : xd[w + 1][lane];
+    for (int s = 0; s < S; ++s) {
+      const float2 dl = (s < S - 1) ? d[s + 1] : xd[w + 1][lane];
       const float2 qz = make_float2(fmaf(sz, lane_next(d[s].x) - d[s].x, rz[s].x),
                                     fmaf(sz, lane_next(d[s].y) - d[s].y, rz[s].y));
-      const float2 ql = make_float2(fmaf(sl[s], dl.x - d[s].x, rl[s].x), fmaf(sl[s], dl.y - d[s].y, rl[s].y));
+      const float sl = (lfwd >> s) & 1u ? step : 0.f;
+      const float2 ql = make_float2(fmaf(sl, dl.x - d[s].x, rl[s].x), fmaf(sl, dl.y - d[s].y, rl[s].y));
       const float m2 = qz.x * qz.x + qz.y * qz.y + ql.x * ql.x + ql.y * ql.y;
       // projection onto |p| <= 1: 1/sqrt(m2) when m2 > 1, else 1 (m2 = 0 included)
       const float sc = fminf(1.f, __builtin_amdgcn_rsqf(m2));
@@ -736,13 +745,21 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
       Pz[s] = cscale(qz, cb);
       Pl[s] = cscale(ql, cb);
     }
+  };
+  // Two steps per turn: the new r takes the registers of the old P and the new
+  // P those of r, so one step per turn ends with a register copy per component.
+  int k = 0;
+  for (; k + 1 < a.n_inner; k += 2) {
+    inner(k);
+    inner(k + 1);
   }
+  if (k < a.n_inner) inner(k);
   // z = v + tau div p  (P holds p after the last step)
-  xr[w + 1][lane] = Pl[TV_S - 1];
+  xr[w + 1][lane] = Pl[S - 1];
   __syncthreads();
-  float2 z[TV_S];
+  float2 z[S];
 #pragma unroll
-  for (int s = 0; s < TV_S; ++s) {
+  for (int s = 0; s < S; ++s) {
     const float2 lp = (s > 0) ? Pl[s - 1] : xr[w][lane];
     const float dx = (Pz[s].x - lane_prev(Pz[s].x)) + (Pl[s].x - lp.x);
     const float dy = (Pz[s].y - lane_prev(Pz[s].y)) + (Pl[s].y - lp.y);
@@ -754,10 +771,10 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
     __syncthreads();
     double acc = 0.0;
 #pragma unroll
-    for (int s = 0; s < TV_S; ++s) {
+    for (int s = 0; s < S; ++s) {
       const int l = l0 + s;
       const float dnx = lane_next(z[s].x), dny = lane_next(z[s].y);
-      const float2 zl = (s < TV_S - 1) ? z[s + 1] : xd[w + 1][lane];
+      const float2 zl = (s < S - 1) ? z[s + 1] : xd[w + 1][lane];
       if (zcore && l >= cl0 && l < cl0 + a.CL && l < Nx) {
         float m2 = 0.f;
         if (zedge) m2 += (dnx - z[s].x) * (dnx - z[s].x) + (dny - z[s].y) * (dny - z[s].y);
@@ -769,7 +786,7 @@ __global__ void __launch_bounds__(1024) tv2d_tile_kernel(Tv2dArgs a) {
     if (threadIdx.x == 0) a.partial[bid] = sum;
   }
 #pragma unroll
-  for (int s = 0; s < TV_S; ++s) {
+  for (int s = 0; s < S; ++s) {
     const int l = l0 + s;
     if (zcore && l >= cl0 && l < cl0 + a.CL && l < Nx) {
       const int64_t idx = ib + (int64_t)l * Nz + n;
@@ -900,19 +917,44 @@ static bool tv_tiled(const ProxGeom& g, int n_inner) {
   return g.lateral_dims == 1 && n_inner >= 1 && n_inner <= TV_MAX_TILED_INNER;
 }
 
-static void tv2d_tiles(const ProxGeom& g, int n_inner, int* CZ, int* CL, int* ntz, int* ntl) {
-  const int H = n_inner + 1;
-  *CZ = 64 - 2 * H;
-  *CL = TV_WAVES * TV_S - 2 * H;
-  *ntz = (g.Nz + *CZ - 1) / *CZ;
-  *ntl = (g.Nx + *CL - 1) / *CL;
+// Tiles of the 2-D step: core sizes and counts.  value: TV(z) is wanted too,
+// which reads z one sample past the core.
+struct Tv2dTiles {
+  int waves, CZ, CL, ntz, ntl;
+};
+
+static Tv2dTiles tv2d_tiles(const ProxGeom& g, int n_inner, bool value) {
+  const int halo = 2 * n_inner + (value ? 2 : 1);
+  auto make = [&](int strip, int waves) {
+    Tv2dTiles t;
+    t.waves = waves;
+    t.CZ = 64 - halo;
+    t.CL = strip * waves - halo;
+    t.ntz = (g.Nz + t.CZ - 1) / t.CZ;
+    t.ntl = (g.Nx + t.CL - 1) / t.CL;
+    return t;
+  };
+  const Tv2dTiles t1 = make(TV_S1, TV_W1), t2 = make(TV_S2, TV_W2);
+  // Loaded samples of the 64 x 72 tiles against those of the 64 x 128 ones, a
+  // sample of the small tiles costing about 0.8 (two workgroups per CU: one
+  // loads and stores while the other computes).  Measured, small against large
+  // (us): 2048 x 1000 with 10 steps 53.0 / 62.1, 13 steps 103 / 106, 16 steps
+  // 138 / 124, 20 steps 259 / 222; 8 x 1024 x 512 with 10 steps 112 / 130, 16
+  // steps 257 / 263; 512 x 64 with 10 steps 19.5 / 25.9.
+  const int64_t n1 = (int64_t)t1.ntz * t1.ntl * TV_S1 * TV_W1, n2 = (int64_t)t2.ntz * t2.ntl * TV_S2 * TV_W2;
+  return n1 * 4 <= n2 * 5 ? t1 : t2;
+}
+
+template <int ST, int WAVES>
+static void tv2d_launch(const Tv2dArgs& a, int nb, float bound, hipStream_t s) {
+  if (bound < INFINITY) hipLaunchKernelGGL((tv2d_tile_kernel<ST, WAVES, true>), dim3(nb), dim3(WAVES * 64), 0, s, a);
+  else hipLaunchKernelGGL((tv2d_tile_kernel<ST, WAVES, false>), dim3(nb), dim3(WAVES * 64), 0, s, a);
 }
 
 int tv_partials(const ProxGeom& g, int n_inner) {
   if (tv_tiled(g, n_inner)) {
-    int CZ, CL, ntz, ntl;
-    tv2d_tiles(g, n_inner, &CZ, &CL, &ntz, &ntl);
-    return ntz * ntl * g.B;
+    const Tv2dTiles t = tv2d_tiles(g, n_inner, true);
+    return t.ntz * t.ntl * g.B;
   }
   const int64_t n = (int64_t)g.B * g.Ny * g.Nx * g.Nz;
   return grid_for(n, 256);
@@ -1040,7 +1082,11 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
     a.Nx = g.Nx;
     a.H = n_inner + 1;
     a.n_inner = n_inner;
-    tv2d_tiles(g, n_inner, &a.CZ, &a.CL, &a.ntz, &a.ntl);
+    const Tv2dTiles t = tv2d_tiles(g, n_inner, partial != nullptr);
+    a.CZ = t.CZ;
+    a.CL = t.CL;
+    a.ntz = t.ntz;
+    a.ntl = t.ntl;
     a.n_total = (int64_t)g.B * g.Nx * g.Nz;
     a.tau = tau;
     a.step = 1.0f / (8.0f * tau);
@@ -1054,8 +1100,8 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
     a.partial = partial;
     a.ntiles = a.ntz * a.ntl * g.B;
     const int nb = (a.ntiles + 7) & ~7;
-    if (bound < INFINITY) hipLaunchKernelGGL(tv2d_tile_kernel<true>, dim3(nb), dim3(TV_WAVES * 64), 0, s, a);
-    else hipLaunchKernelGGL(tv2d_tile_kernel<false>, dim3(nb), dim3(TV_WAVES * 64), 0, s, a);
+    if (t.waves == TV_W1) tv2d_launch<TV_S1, TV_W1>(a, nb, bound, s);
+    else tv2d_launch<TV_S2, TV_W2>(a, nb, bound, s);
     return hipGetLastError();
   }
   TvIdx d;
