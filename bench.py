@@ -138,19 +138,19 @@ def phi_sizes_bench() -> dict:
 # kernels of the single-kernel stages (a volume's lateral stages take two or
 # three launches of the lateral kernel), by the name rocprofv3 reports
 STAGE_KERNEL = {
-    "nufft_fwd": "nufft_fwd_pair_kernel<6, false, false>",
-    "nufft_adj": "nufft_adj_pair_kernel<6, true>",
-    "nufft_normal": "nufft_normal_pair_kernel<6, false, 4>",
-    "prox": {"tv": "tv2d_tile_kernel<false>", "haar": "haar_kernel<3, 3", "l1": "prox_l1_kernel"},
+    "nufft_fwd": "column_pair_kernel<6, 0, ",
+    "nufft_adj": "column_pair_kernel<6, 1, ",
+    "nufft_normal": "column_pair_kernel<6, 2, ",
+    "prox": {"tv": "tv2d_tile_kernel<9, 8, false>", "haar": "haar_kernel<3, 3", "l1": "prox_l1_kernel"},
 }
 BSCAN_STAGE_KERNEL = {
-    "lat_fwd": "lat_kernel<0, false, ",
-    "normal": "lat_kernel<3, false, ",
-    "lat_update": "lat_kernel<4, false, ",
+    "lat_fwd": "lat_kernel<0, 2, ",
+    "normal": "lat_kernel<3, 2, ",
+    "lat_update": "lat_kernel<4, 2, ",
 }
 STAGE_SOURCE = {
     "lat_fwd": "oct_lateral.hip", "normal": "oct_lateral.hip", "lat_update": "oct_lateral.hip",
-    "nufft_fwd": "oct_nufft.hip", "nufft_adj": "oct_nufft.hip", "nufft_normal": "oct_nufft.hip",
+    "nufft_fwd": "oct_column.hip", "nufft_adj": "oct_column.hip", "nufft_normal": "oct_column.hip",
     "prox": "oct_prox.hip",
 }
 
