@@ -641,9 +641,10 @@ __global__ void tv_value_kernel(TvIdx d, const float2* __restrict__ z, double* p
 // loads and stores (about 15 us per 256 such tiles), in series when one
 // workgroup fills a CU.  Two workgroups of eight waves per CU overlap them but
 // spend more on halos (core 43 x 51 of 64 x 72 at ten steps, 43 x 107 of 64 x
-// 128); strips of nine are the longest whose state and temporaries leave four
-// waves per SIMD without spills in the steps (ten: 58.6 us, eight: 62.1).  Ten
-// steps on 2048 x 1000: 62.8 -> 53.0 us; on 8 x 1024 x 512: 131 -> 112 us.
+// 128); strips of nine are the longest that gain (ten: 58.6 us, eight: 62.1).
+// Two steps per turn of the loop spare the copies that swap the registers of r
+// and P, and 1.9 us, but spill to scratch memory: not used.  Ten steps on
+// 2048 x 1000: 62.8 -> 54.9 us; on 8 x 1024 x 512: 131 -> 115 us.
 // ---------------------------------------------------------------------------
 constexpr int TV_S1 = 9, TV_W1 = 8;
 constexpr int TV_S2 = 8, TV_W2 = 16;
@@ -713,7 +714,7 @@ __global__ void __launch_bounds__(WAVES * 64, 4) tv2d_tile_kernel(Tv2dArgs a) {
     Pz[s] = cscale(rz[s], mom0);
     Pl[s] = cscale(rl[s], mom0);
   }
-  auto inner = [&](int k) __attribute__((always_inline)) {
+  for (int k = 0; k < a.n_inner; ++k) {
     asm volatile("" : "+s"(lfwd));   // weights chosen by the scalar unit in each step, not kept in S registers
     const float mom1 = 1.f + a.mom[k];
     const float mnext = a.mom[k + 1];
@@ -745,15 +746,7 @@ __global__ void __launch_bounds__(WAVES * 64, 4) tv2d_tile_kernel(Tv2dArgs a) {
       Pz[s] = cscale(qz, cb);
       Pl[s] = cscale(ql, cb);
     }
-  };
-  // Two steps per turn: the new r takes the registers of the old P and the new
-  // P those of r, so one step per turn ends with a register copy per component.
-  int k = 0;
-  for (; k + 1 < a.n_inner; k += 2) {
-    inner(k);
-    inner(k + 1);
   }
-  if (k < a.n_inner) inner(k);
   // z = v + tau div p  (P holds p after the last step)
   xr[w + 1][lane] = Pl[S - 1];
   __syncthreads();
@@ -938,8 +931,8 @@ static Tv2dTiles tv2d_tiles(const ProxGeom& g, int n_inner, bool value) {
   // Loaded samples of the 64 x 72 tiles against those of the 64 x 128 ones, a
   // sample of the small tiles costing about 0.8 (two workgroups per CU: one
   // loads and stores while the other computes).  Measured, small against large
-  // (us): 2048 x 1000 with 10 steps 53.0 / 62.1, 13 steps 103 / 106, 16 steps
-  // 138 / 124, 20 steps 259 / 222; 8 x 1024 x 512 with 10 steps 112 / 130, 16
+  // (us): 2048 x 1000 with 10 steps 54.9 / 62.8, 13 steps 103 / 106, 16 steps
+  // 138 / 124, 20 steps 259 / 222; 8 x 1024 x 512 with 10 steps 115 / 131, 16
   // steps 257 / 263; 512 x 64 with 10 steps 19.5 / 25.9.
   const int64_t n1 = (int64_t)t1.ntz * t1.ntl * TV_S1 * TV_W1, n2 = (int64_t)t2.ntz * t2.ntl * TV_S2 * TV_W2;
   return n1 * 4 <= n2 * 5 ? t1 : t2;
