@@ -12,8 +12,8 @@
 //   4096 points took three).  The first forward stage reads the column from
 //   memory once for both rows, the last inverse stage joins them into it.
 // * Samples by grid cell.  Consecutive samples are at least one cell apart
-//   (t' >= K dz dk / pi, checked on the host), so a cell is the base cell of at
-//   most one sample.  A thread owns SPT consecutive base cells, finds the
+//   (t' >= K dz dk / pi), and the host takes these kernels where a cell is the
+//   base cell of at most one sample.  A thread owns SPT consecutive base cells, finds the
 //   sample of each by inverting t(m), and its windows overlap: SPT + J - 1
 //   cells are read, and added to, for SPT samples (J SPT of each before), the
 //   weights serve both directions, and the adjoint needs no pass per tap: a
@@ -38,13 +38,11 @@ constexpr int KBH = (OCT_KB_DEG + 1) / 2;
 constexpr int COL_PADK = 8;    // wrapped cells after each row
 constexpr double COL_EPS = 0x1p-13;   // 1.2e-4; 1 - COL_EPS is exact
 
-// Base cell of t: floor(t + COL_EPS).  The coordinates of the q = 0 column are
-// integers, so a boundary at the integers would fall between cells by
-// rounding; a boundary COL_EPS below them is crossed only where t drifts by
-// more than its rounding error from one sample to the next (t's drift past
-// one cell per sample at the crossing is COL_EPS / t >= 3e-9 cells, its
-// rounding error 1e-9), so two samples never share a cell.  The window's value
-// COL_EPS beyond its edge is below 4e-8 of its peak (J = 6).
+// Base cell of t: floor(t + COL_EPS), which no two samples of a column share
+// where col_cells_distinct says so.  The q = 0 coordinates t_0 + h m (h >= 1
+// cells apart) are integers for the usual optics, and a boundary at the integers
+// would fall between cells by rounding; COL_EPS below them it does not.  The
+// window's value COL_EPS beyond its edge is below 4e-8 of its peak (J = 6).
 
 __device__ __forceinline__ double col_sqrt(double arg) {   // arg > 0; relative error ~2e-14
   const double r0 = (double)__builtin_amdgcn_rsqf(fmaxf((float)arg, 1e-30f));
@@ -747,12 +745,32 @@ int col_threads(const ColArgs& a, int* spt, int* mb) {
   return nt <= 1024 ? nt : 0;
 }
 
-// K = 2 N with a transform plan, samples at least one cell apart (spacing
-// along k at q = 0, the smallest; up to rounding), and a column's span within
-// the grid
+// Whether no two samples of a column have the same base cell.  For h well above
+// one cell they cannot.  At h = 1 (the default pitch) a column's t_m falls short
+// of t_0 + h m by delta, which shrinks along m by delta / t a sample: where the
+// boundary lies g below the fraction of t_0 + h m (modulo 1), a column passes it
+// with delta = g, or g + 1, ..., and the two samples beside it stay apart if that
+// drift exceeds the rounding of t (7e-10: col_sqrt at t < 32000, checked at plan
+// creation).  So g must not be small, nor within rounding of 1: COL_EPS - 1e-5
+// (3.5e-9 a sample, less the 1e-9 that h may lack) to 1 - 1e-6.  Other fractions
+// (about 1.2e-4 of them) leave the columns to the pair kernels, which look for
+// equal base cells.
+static bool col_cells_distinct(const ColArgs& a) {
+  const double h = 2.0 * a.ct * a.dk;
+  if (h < 1.0 - 1e-9) return false;
+  if (h > 1.0 + 1e-8) return true;
+  const double t0 = 2.0 * a.ct * a.k_min, phi = t0 - std::floor(t0), end = phi + (h - 1.0) * (a.Mk - 1);
+  const double lo = std::min(phi, end), hi = std::max(phi, end);
+  for (int c = -1; c <= 1; ++c)   // the fractions with a small g, or one close to 1
+    if (hi > c - COL_EPS - 1e-6 && lo < c - 1e-5) return false;
+  return true;
+}
+
+// K = 2 N with a transform plan, distinct base cells, and a column's span
+// within the grid
 bool col_supported(const ColArgs& a) {
   int spt = 0, mb = 0;
-  return a.f.ns > 0 && 2.0 * a.ct * a.dk >= 1.0 - 1e-9 &&
+  return a.f.ns > 0 && col_cells_distinct(a) &&
          a.span + a.J - 1 <= 2 * a.Nz && col_lds_bytes(a.Nz) <= 150 * 1024 && col_threads(a, &spt, &mb) > 0;
 }
 

@@ -1,0 +1,78 @@
+"""The library's host code on the CPU: liboct on a HIP runtime without a device
+(tests/sanitize/hip_stub.c), whose launches leave the kernels' names.  Which
+kernels a plan's calls take."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+STUB = os.path.join(HERE, "sanitize", "hip_stub.c")
+LIB = os.path.join(os.path.dirname(HERE), "paper_2108_01438_amd", "liboct.so")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    d = tmp_path_factory.mktemp("hip_stub")
+    out = os.path.join(d, "libamdhip64.so.7")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7", STUB, "-o", out], check=True)
+    return out
+
+
+# A process of its own: this one may hold the real runtime under the same name.
+CHILD = r"""
+import ctypes, math, struct, sys
+stub = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+stub.stub_log.restype = ctypes.c_char_p
+P = ctypes.c_void_p
+BUF = P(4096)
+
+def plan(n_depth, n_x, n_k, n_y=1, lateral_dims=1, kb_width=6, batch=1, k_min=2 * math.pi / 0.9, k_max=2 * math.pi / 0.75,
+         dz=0.0, masked=False):
+    g = struct.pack("<ii5q11dii", lateral_dims, kb_width, n_depth, n_x, n_y, n_k, batch, k_min, k_max, 2.0, 2.0, dz, -1.0,
+                    5.0, 1e-3, 0.0, 2.0, 0.0, 0, 0)
+    mask = (b"\1\0" * (n_x * n_y * n_k))[:n_x * n_y * n_k] if masked else None
+    h = P()
+    st = lib.oct_plan_create(ctypes.c_char_p(g), ctypes.c_char_p(mask), ctypes.byref(h))
+    assert st == 0, (st, n_depth)
+    return h
+
+def kernels(f, *args):
+    stub.stub_log_clear()
+    st = f(*args)
+    return st, [l.split()[0] for l in stub.stub_log().decode().splitlines()]
+
+def columns(names):
+    return [n for n in names if "column_pair" in n or "nufft" in n]
+"""
+
+
+def run_child(stub, code):
+    r = subprocess.run([sys.executable, "-c", CHILD + code, stub, LIB], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return r.stdout
+
+
+def test_columns_by_grid_cell_only_with_distinct_cells(stub):
+    """Samples are found by grid cell only where rounding cannot put two of them into one: not where
+    the q = 0 coordinates k_min / dk + m lie within 2^-13 below an integer."""
+    out = run_child(stub, r"""
+eps = 2.0 ** -13
+for n, t0, h, cell in [
+    (512, 2560.0, 1.0, True), (512, 2560.0 - 1e-9, 1.0, True), (512, 2560.5, 1.0, True), (512, 2561.0 - 2 * eps, 1.0, True),
+    (512, 2561.0 - eps, 1.0, False), (1024, 20001.0 - eps + 1e-11, 1.0, False), (512, 2561.0 - eps - 1e-8, 1.0, False),
+    (2048, 9000.0 - 0.5 * eps, 1.0, False), (512, 2561.0 - 2e-5, 1.0, False),
+    # half a cell more per sample than one, or a band over which the fraction runs into the boundary
+    (512, 2561.0 - eps, 1.5, True), (512, 2561.0 - eps - 2e-6, 1.0 + 5e-9, False), (512, 2561.0 - 3e-4, 0.999, False),
+]:
+    dk = 1.4 / n                       # t = K dz / pi (k_min + m dk): h cells a sample
+    h_plan = plan(n, 6, n - 1, k_min=t0 * dk / h, k_max=(t0 / h + n - 2) * dk, dz=h * math.pi / (2 * n * dk) if h != 1 else 0.0)
+    for f, args in ((lib.oct_forward, (BUF, BUF, None)), (lib.oct_adjoint, (BUF, BUF, None)), (lib.oct_grad, (BUF, BUF, BUF, None, None))):
+        st, names = kernels(f, h_plan, *args)
+        got = columns(names)
+        assert st == 0 and got and all(("column_pair" in k) == cell for k in got), (n, t0, h, cell, got)
+print("ok")
+""")
+    assert out.strip() == "ok"
