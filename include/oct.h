@@ -292,8 +292,9 @@ typedef enum {
  * adjoint columns in one kernel per column pair (or the two pair kernels
  * when a pair's samples do not fit its registers); OCT_E_UNSUPPORTED on a
  * masked plan.  The other stages still run as named: OCT_STAGE_NUFFT_FWD
- * then writes the residual spectrum, and OCT_STAGE_NORMAL runs the general
- * seam.  Asynchronous. */
+ * then runs oct_forward's columns, or where the solve takes the two pair
+ * kernels writes the residual spectrum as its first one does, and
+ * OCT_STAGE_NORMAL runs the general seam.  Asynchronous. */
 oct_status oct_run_stage(oct_plan_t plan, int32_t stage, int32_t penalty, const float* y, void* stream);
 
 /* Direct (non-iterative) reconstructions of Sec. 3.1: the three images of

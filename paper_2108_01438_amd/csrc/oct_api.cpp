@@ -1541,8 +1541,8 @@ oct_status oct_run_stage(oct_plan_t p, int32_t stage, int32_t pen, const float* 
   switch (stage) {
     case OCT_STAGE_LAT_FWD:
       return run_lat_forward(p, nullptr, p->za, p->zb, 0.5f, s, p->xext);
-    case OCT_STAGE_NUFFT_FWD:   // as in a solve without the objective
-      if (spectral_seam(p, false)) return run_cols_fwd_res(p, p->yhat, nullptr, nullptr, s);
+    case OCT_STAGE_NUFFT_FWD:   // as in a solve without the objective (one by grid cell fuses it with the adjoint)
+      if (spectral_seam(p, false) && !p->col) return run_cols_fwd_res(p, p->yhat, nullptr, nullptr, s);
       OCTCHK(run_cols_fwd(p, s, p->hs));
       return OCT_OK;
     case OCT_STAGE_NORMAL: {

@@ -1285,6 +1285,7 @@ hipError_t nufft_fwd_pair_t(const NufftArgs& a, const float2* X1, float2* Wh, co
 
 template <bool RES>
 hipError_t fwd_pair_dispatch(const NufftArgs& a, const float2* X1, float2* Wh, const PairRes& r, hipStream_t s) {
+  if (!nufft_pair_supported(a)) return hipErrorInvalidConfiguration;   // some butterflies would have no thread
   const int nt = pair_threads(a, false);
   const bool one = fft_one(a.fK, 2, nt);
   switch (a.J) {
@@ -1386,6 +1387,7 @@ hipError_t launch_nufft_normal_pair(const NufftArgs& a, const float2* X1, const 
 }
 
 hipError_t launch_nufft_adj_pair(const NufftArgs& a, const float2* Rh, float2* X, hipStream_t s) {
+  if (!nufft_pair_supported(a)) return hipErrorInvalidConfiguration;
   const int nt = pair_threads(a, true);
   const bool one = fft_one(a.fK, 2, nt);
   switch (a.J) {

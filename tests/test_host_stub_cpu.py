@@ -28,6 +28,7 @@ lib = ctypes.CDLL(sys.argv[2])
 stub.stub_log.restype = ctypes.c_char_p
 P = ctypes.c_void_p
 BUF = P(4096)
+BUF8 = ctypes.byref(ctypes.c_double())
 
 def plan(n_depth, n_x, n_k, n_y=1, lateral_dims=1, kb_width=6, batch=1, k_min=2 * math.pi / 0.9, k_max=2 * math.pi / 0.75,
          dz=0.0, masked=False):
@@ -73,6 +74,35 @@ for n, t0, h, cell in [
         st, names = kernels(f, h_plan, *args)
         got = columns(names)
         assert st == 0 and got and all(("column_pair" in k) == cell for k in got), (n, t0, h, cell, got)
+print("ok")
+""")
+    assert out.strip() == "ok"
+
+
+def test_stages_run_the_kernels_of_the_calls(stub):
+    """oct_run_stage launches what oct_forward, oct_adjoint and oct_grad launch, fully observed or
+    masked, where the columns run by grid cell (1225: its K-point rows fit no pair kernel) and where
+    they do not (2000)."""
+    out = run_child(stub, r"""
+for n in (512, 1225, 1400, 2000):
+    for masked in (False, True):
+        p = plan(n, 4, n, masked=masked)
+        cell = n != 2000
+        def stage(k):
+            st, names = kernels(lib.oct_run_stage, p, k, 0, BUF, None)
+            assert st == 0
+            return columns(names)
+        fwd, adj = columns(kernels(lib.oct_forward, p, BUF, BUF, None)[1]), columns(kernels(lib.oct_adjoint, p, BUF, BUF, None)[1])
+        both = columns(kernels(lib.oct_lipschitz, p, 1, ctypes.c_uint64(0), 0, BUF8, None)[1])
+        assert len(fwd) == len(adj) == 1 and len(both) == (2 if masked else 1)
+        assert all(("column_pair" in k) == cell for k in fwd + adj + both), (n, fwd, adj, both)
+        assert stage(3) == adj
+        if masked or cell:
+            assert stage(1) == fwd, (n, masked, stage(1), fwd)
+        else:
+            assert len(stage(1)) == 1
+        if not masked:
+            assert stage(6) == both
 print("ok")
 """)
     assert out.strip() == "ok"
