@@ -846,11 +846,15 @@ oct_status check_dtcwt(const oct_plan* p, int levels) {
   return OCT_OK;
 }
 
+Dual3 solver_dual(const oct_plan* p, float2* d) {   // the images of p0 or p1 (a B-scan's two: not used)
+  return p->lat_dims == 2 ? Dual3{{d, d + p->n_img(), d + 2 * p->n_img()}} : Dual3{};
+}
+
 // z = prox(v) with FP64 partials of R(z) in p->partial[0..*np) (for the DT-CWT
 // only when want_value: R(z) then needs a transform of z of its own); the TV
-// dual goes from p_in to p_out, p_scratch (nullable, may be p_in) is clobbered
+// dual goes from p_in to p_out; volumes clobber scratch, which may be p_in
 oct_status run_prox(oct_plan* p, int pen, float tau, float bound, int tv_inner, int haar_levels, const float2* v,
-                    float2* z, const float2* p_in, float2* p_out, float2* p_scratch, int* np, hipStream_t s,
+                    float2* z, const float2* p_in, float2* p_out, const Dual3& scratch, int* np, hipStream_t s,
                     bool want_value = false) {
   ProxGeom pg = prox_geom(p);
   if (pen == OCT_PEN_L1) {
@@ -868,7 +872,7 @@ oct_status run_prox(oct_plan* p, int pen, float tau, float bound, int tv_inner, 
     std::vector<float> mom = fgp_momenta(tv_inner);
     // TV(z) partials only when the value is wanted (the kernels skip it otherwise)
     // X1 is free between the lateral passes: scratch of the volume path
-    HIPCHK(launch_prox_tv(pg, tv_inner, mom.data(), v, z, p_in, p_out, p_scratch, tau, bound,
+    HIPCHK(launch_prox_tv(pg, tv_inner, mom.data(), v, z, p_in, p_out, scratch, tau, bound,
                           want_value ? p->partial : nullptr, p->tvwork, p->X1, s));
     *np = want_value ? tv_partials(pg, tv_inner) : 0;
   } else if (pen == OCT_PEN_DTCWT) {
@@ -1296,16 +1300,16 @@ oct_status oct_prox(oct_plan_t p, int32_t pen, double lambda, double delta, int3
       return OCT_OK;
     }
     const int64_t npel = p->n_img() * (p->lat_dims + 1);
-    // scratch of the volume path: the caller's dual (replaced below in any case),
-    // or p1 unless a resumed solve may still need it
-    float2* scratch = state ? (float2*)state : p->tv_last != p->p1 ? p->p1 : nullptr;
-    OCTCHK(run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, (const float2*)state,
-                    p->p0, scratch, &np, s));
-    if (state) HIPCHK(launch_copy(p->p0, (float2*)state, npel, s));
+    // not the dual that a resumed solve may start from; the solver's images hold
+    // nothing between calls
+    float2* pout = p->tv_last == p->p0 ? p->p1 : p->p0;
+    OCTCHK(run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, (const float2*)state, pout,
+                    Dual3{{p->xext, p->za, p->zb}}, &np, s));
+    if (state) HIPCHK(launch_copy(pout, (float2*)state, npel, s));
     return OCT_OK;
   }
-  return run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, nullptr, nullptr, nullptr,
-                  &np, s);
+  return run_prox(p, pen, tau, bf, tv_inner, haar_levels, (const float2*)v, (float2*)z, nullptr, nullptr, Dual3{}, &np,
+                  s);
 }
 
 oct_status oct_dtcwt_filter(int32_t which, float* h0, int32_t* n) {
@@ -1505,7 +1509,7 @@ oct_status oct_mbir_solve(oct_plan_t p, const float* y, const oct_solve_params* 
         double* save = p->partial;
         p->partial = pen_part;
         oct_status st = run_prox(p, prm->penalty, tau, bf, prm->tv_inner, prm->haar_levels, p->xext, zo, pin, pout,
-                                 pout == p->p0 ? p->p1 : p->p0, &npen, s, want_obj);
+                                 solver_dual(p, pout == p->p0 ? p->p1 : p->p0), &npen, s, want_obj);
         p->partial = save;
         OCTCHK(st);
         if (prm->penalty == OCT_PEN_TV) {
@@ -1577,7 +1581,7 @@ oct_status oct_run_stage(oct_plan_t p, int32_t stage, int32_t pen, const float* 
     case OCT_STAGE_PROX: {
       int np = 0;
       return run_prox(p, pen, 1e-3f, INFINITY, 10, 3, p->xext, p->zb, pen == OCT_PEN_TV ? p->p0 : nullptr,
-                      pen == OCT_PEN_TV ? p->p1 : nullptr, p->p0, &np, s);
+                      pen == OCT_PEN_TV ? p->p1 : nullptr, solver_dual(p, p->p0), &np, s);
     }
     default:
       return fail(OCT_E_INVALID, "unknown stage");

@@ -301,11 +301,14 @@ int haar_partials(const ProxGeom& g, int levels);
 hipError_t launch_prox_haar(const ProxGeom& g, int levels, const float2* v, float2* z,
                             float tau, double* partial, hipStream_t s);
 int tv_partials(const ProxGeom& g, int n_inner);
-// p_in (nullable: zero) -> p_out.  Volumes also use z (before it receives the
-// result), img_scratch (one image) and p_scratch (a dual; may be p_in, whose
-// content is then lost; NULL: slower) as scratch.
+// p_in (nullable: zero) -> p_out.  Volumes also use as scratch z (before it
+// receives the result), img_scratch (one image) and scratch (a dual's three
+// images; may be p_in's, whose content is then lost).
+struct Dual3 {
+  float2* c[3];   // by component: depth, x, y
+};
 hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, const float2* v,
-                          float2* z, const float2* p_in, float2* p_out, float2* p_scratch, float tau,
+                          float2* z, const float2* p_in, float2* p_out, const Dual3& scratch, float tau,
                           float bound, double* partial, float2* work, float2* img_scratch, hipStream_t s);
 size_t tv_work_elems(const ProxGeom& g);
 // DT-CWT: z = W^T soft_tau(W v); work holds dtcwt_work_elems complex values

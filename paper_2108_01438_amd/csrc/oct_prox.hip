@@ -1015,49 +1015,33 @@ static hipError_t tv3d_pass(const ProxGeom& g, int T, const float2* v, float2* c
 // Inner steps of the 3-D path.  Runs of T steps (3 and 2) alternate between two
 // pairs of duals, {last, previous} each: one pair holds p_out, the other is
 // made of the scratch (work: four images, z and img_scratch: one each, z being
-// written only after the steps; and p_scratch, three, which may be p_in: it is
-// read by the first pass only).  Without p_scratch: one step at a time over
-// three duals.
+// written only after the steps; and scratch, three, which may be p_in: it is
+// read by the first pass only, which does not write scratch).
 static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, const float2* v, float2* z,
-                             const float2* p_in, float2* p_out, float2* p_scratch, float tau, float bound,
+                             const float2* p_in, float2* p_out, const Dual3& scratch, float tau, float bound,
                              float2* work, float2* img_scratch, hipStream_t s) {
-  struct Dual {
-    float2* c[3];
-  };
   const int64_t n = (int64_t)g.B * g.Ny * g.Nx * g.Nz;
   auto packed = [&](const float2* p) {
     float2* q = const_cast<float2*>(p);
-    return q ? Dual{{q, q + n, q + 2 * n}} : Dual{{nullptr, nullptr, nullptr}};
+    return q ? Dual3{{q, q + n, q + 2 * n}} : Dual3{{nullptr, nullptr, nullptr}};
   };
-  const Dual in = packed(p_in), out = packed(p_out), s1 = packed(work), s2{{work + 3 * n, z, img_scratch}},
-             none = packed(nullptr);
-  const int maxT = p_scratch ? TV3_MAX_T : 1;
-  const int passes = (n_inner + maxT - 1) / maxT;   // of at most maxT steps, as even as possible
-  Dual last = in, prev = none;
+  const Dual3 in = packed(p_in), out = packed(p_out), s1 = packed(work), s2{{work + 3 * n, z, img_scratch}},
+              none = packed(nullptr);
+  const int passes = (n_inner + TV3_MAX_T - 1) / TV3_MAX_T;   // of at most TV3_MAX_T steps, as even as possible
+  Dual3 last = in, prev = none;
   int k = 0;
   for (int i = 0; i < passes; ++i) {
     const int T = (n_inner - k + (passes - i) - 1) / (passes - i);
     const int left = passes - 1 - i;
-    Dual o, op = none;   // where this pass leaves its last two duals
-    if (maxT == 1) {
-      o = left % 3 == 0 ? out : left % 3 == 1 ? s1 : s2;
-    } else {
-      // the pair with p_out when an even number of passes is left; the other
-      // duals of the pairs: p_scratch is not written by the first pass
-      const bool outer = left % 2 == 0;
-      const bool scratch_with_out = passes % 2 == 0;
-      if (outer) {
-        o = out;
-        op = scratch_with_out ? packed(p_scratch) : s1;
-      } else {
-        o = s2;
-        op = scratch_with_out ? s1 : packed(p_scratch);
-      }
-      if (left == 0) op = none;   // nothing follows the last pass
-    }
+    // where this pass leaves its last two duals: the pair with p_out when an even
+    // number of passes is left (nothing follows the last one); scratch is in the
+    // pair that the first pass does not write
+    const bool outer = left % 2 == 0, scratch_with_out = passes % 2 == 0;
+    const Dual3 o = outer ? out : s2;
+    const Dual3 op = left == 0 ? none : outer == scratch_with_out ? scratch : s1;
     const hipError_t e = tv3d_pass(g, T, v, last.c, prev.c, k > 0 ? mom[k - 1] : 0.f, mom + k, o.c, op.c, tau, bound, s);
     if (e != hipSuccess) return e;
-    prev = maxT == 1 ? last : op;
+    prev = op;
     last = o;
     k += T;
   }
@@ -1067,7 +1051,7 @@ static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, c
 // p_in (nullable = zero) -> p_out; z = v + tau div p_out; partial (nullable:
 // not computed) = TV(z).
 hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, const float2* v, float2* z,
-                          const float2* p_in, float2* p_out, float2* p_scratch, float tau, float bound,
+                          const float2* p_in, float2* p_out, const Dual3& scratch, float tau, float bound,
                           double* partial, float2* work, float2* img_scratch, hipStream_t s) {
   if (tv_tiled(g, n_inner)) {
     Tv2dArgs a{};
@@ -1127,7 +1111,7 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
       hipLaunchKernelGGL(tv_step_kernel, dim3(gb), dim3(256), 0, s, d, dd, r, p_out, step, mom[k]);
     }
   } else {
-    const hipError_t e = tv3d_steps(g, n_inner, mom, v, z, p_in, p_out, p_scratch, tau, bound, work, img_scratch, s);
+    const hipError_t e = tv3d_steps(g, n_inner, mom, v, z, p_in, p_out, scratch, tau, bound, work, img_scratch, s);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(tv_div_kernel, dim3(gb), dim3(256), 0, s, d, v, p_out, tau, bound, z);
