@@ -15,6 +15,8 @@
 // All partial sums are per block in FP64 and summed in a fixed order.
 #include "oct_fft.h"
 
+#include <algorithm>
+
 namespace {
 
 __device__ double block_sum(double v, double* sh) {
@@ -378,25 +380,38 @@ __global__ void tv_div_kernel(TvIdx d, const float2* __restrict__ v, const float
 }
 
 __global__ void tv_step_kernel(TvIdx d, const float2* __restrict__ dd, float2* r, float2* p, float step, float mom) {
-  const int64_t sx = d.Nz;
+  const int64_t sx = d.Nz, sy = (int64_t)d.Nx * d.Nz;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < d.n; i += (int64_t)gridDim.x * blockDim.x) {
     int iz, ix, iy;
     tv_coords(d, i, iz, ix, iy);
     const float2 c = dd[i];
     float2 gz = (iz < d.Nz - 1) ? csub(dd[i + 1], c) : make_float2(0.f, 0.f);
     float2 gx = (ix < d.Nx - 1) ? csub(dd[i + sx], c) : make_float2(0.f, 0.f);
-    float2 pz = r[i], px = r[d.n + i];
+    float2 gy = make_float2(0.f, 0.f);
+    if (d.nd == 3 && iy < d.Ny - 1) gy = csub(dd[i + sy], c);
+    float2 pz = r[i], px = r[d.n + i], py = make_float2(0.f, 0.f);
     pz = make_float2(pz.x + step * gz.x, pz.y + step * gz.y);
     px = make_float2(px.x + step * gx.x, px.y + step * gx.y);
-    const float m2 = pz.x * pz.x + pz.y * pz.y + px.x * px.x + px.y * px.y;
+    float m2 = pz.x * pz.x + pz.y * pz.y + px.x * px.x + px.y * px.y;
+    if (d.nd == 3) {
+      py = r[2 * d.n + i];
+      py = make_float2(py.x + step * gy.x, py.y + step * gy.y);
+      m2 += py.x * py.x + py.y * py.y;
+    }
     const float sc = m2 > 1.f ? 1.f / sqrtf(m2) : 1.f;
     pz = cscale(pz, sc);
     px = cscale(px, sc);
+    py = cscale(py, sc);
     const float2 oz = p[i], ox = p[d.n + i];
     r[i] = make_float2(pz.x + mom * (pz.x - oz.x), pz.y + mom * (pz.y - oz.y));
     r[d.n + i] = make_float2(px.x + mom * (px.x - ox.x), px.y + mom * (px.y - ox.y));
     p[i] = pz;
     p[d.n + i] = px;
+    if (d.nd == 3) {
+      const float2 oy = p[2 * d.n + i];
+      r[2 * d.n + i] = make_float2(py.x + mom * (py.x - oy.x), py.y + mom * (py.y - oy.y));
+      p[2 * d.n + i] = py;
+    }
   }
 }
 
@@ -953,30 +968,79 @@ int tv_partials(const ProxGeom& g, int n_inner) {
   return grid_for(n, 256);
 }
 
-// Planes along y per workgroup: the pass takes rounds of workgroups over the
-// 256 CUs (one resident per CU), each CY planes and 2 T of halo long.
-static hipError_t tv3d_pass(const ProxGeom& g, int T, const float2* v, float2* const* p, float2* const* po, float m0,
-                            const float* mom, float2* const* out, float2* const* out_prev, float tau, float bound,
-                            hipStream_t s) {
+// Planes along y per workgroup (CY) and runs of planes (nty): the pass takes
+// rounds of workgroups over the 256 CUs (one resident per CU), each CY planes
+// and 2 T of halo long.
+struct Tv3dSplit {
+  int ntz, ntl, nty, CY;
+  int64_t cols, rounds;
+};
+
+static Tv3dSplit tv3d_split(const ProxGeom& g, int T) {
+  Tv3dSplit s{};
+  const int CZ = 64 - 2 * T, CL = TV3_ROWS - 2 * T;
+  s.ntz = (g.Nz + CZ - 1) / CZ;
+  s.ntl = (g.Nx + CL - 1) / CL;
+  s.cols = (int64_t)s.ntz * s.ntl * g.B;
+  int64_t best = INT64_MAX;
+  for (int n = 1; n <= g.Ny; ++n) {
+    const int cy = (g.Ny + n - 1) / n, nty = (g.Ny + cy - 1) / cy;
+    const int64_t rounds = (s.cols * nty + 255) / 256, cost = rounds * (cy + 2 * T + 2);
+    if (cost < best) {
+      best = cost;
+      s.CY = cy;
+      s.nty = nty;
+      s.rounds = rounds;
+    }
+  }
+  return s;
+}
+
+static int tv3d_passes(int n_inner) { return (n_inner + TV3_MAX_T - 1) / TV3_MAX_T; }
+static int tv3d_pass_steps(int left, int passes_left) {   // as even as possible
+  return (left + passes_left - 1) / passes_left;
+}
+
+// Whether a volume takes the walk along y (its passes by steps in split, zero on
+// entry) or two kernels per step (d = v + tau div r stored, then r and p).  A
+// pass of the walk is a chain of planes (1.9, 3.1 and 4.9 us each with 1, 2 and 3
+// steps; 1.9, 2.4 and 3.7 in the first pass, which reads one dual), three and
+// more of them halo, however small the volume.  The two kernels take 5 to 7 us a
+// step, as fast as the host launches them, until the memory traffic shows (24 us
+// per million samples), and copy the dual once.  So small volumes, and those a
+// few rows wide (an empty tile costs as much), keep the two kernels for more than
+// a few steps.  Measured, walk against two kernels, 10 steps (us): 128 x 16 x 16
+// 103 / 88, 2048 x 8 x 8 125 / 87, 1024 x 4 x 100 208 / 148, 1024 x 1 x 256
+// 359 / 120, 512 x 20 x 20 120 / 104; 256 x 40 x 45 137 / 149, 512 x 32 x 32
+// 146 / 168, 512 x 64 x 64 274 / 556; three steps on 128 x 16 x 16 31 / 28 to 37.
+static bool tv3d_walks(const ProxGeom& g, int n_inner, Tv3dSplit* split) {
+  static const double first_us[TV3_MAX_T + 1] = {0, 1.9, 2.4, 3.7}, plane_us[TV3_MAX_T + 1] = {0, 1.9, 3.1, 4.9};
+  const double mpx = 1e-6 * (double)g.B * g.Ny * g.Nx * g.Nz;
+  const double two = std::max(10.5, 13.3 * mpx) + n_inner * std::max(6.5, 3.5 + 24.0 * mpx);
+  double walk = 0.0;
+  const int passes = tv3d_passes(n_inner);
+  for (int i = 0, k = 0; i < passes; ++i) {
+    const int T = tv3d_pass_steps(n_inner - k, passes - i);
+    Tv3dSplit& s = split[T];
+    if (s.rounds == 0) s = tv3d_split(g, T);
+    walk += 2.5 + (double)s.rounds * (s.CY + 2 * T) * (i == 0 ? first_us : plane_us)[T];
+    k += T;
+  }
+  return 1.05 * walk < two;
+}
+
+static hipError_t tv3d_pass(const ProxGeom& g, const Tv3dSplit& sp, int T, const float2* v, float2* const* p,
+                            float2* const* po, float m0, const float* mom, float2* const* out,
+                            float2* const* out_prev, float tau, float bound, hipStream_t s) {
   Tv3dArgs a{};
   a.Nz = g.Nz;
   a.Nx = g.Nx;
   a.Ny = g.Ny;
-  const int CZ = 64 - 2 * T, CL = TV3_ROWS - 2 * T;
-  a.ntz = (g.Nz + CZ - 1) / CZ;
-  a.ntl = (g.Nx + CL - 1) / CL;
-  const int64_t cols = (int64_t)a.ntz * a.ntl * g.B;
-  int64_t best = INT64_MAX;
-  for (int n = 1; n <= g.Ny; ++n) {
-    const int cy = (g.Ny + n - 1) / n, nty = (g.Ny + cy - 1) / cy;
-    const int64_t cost = ((cols * nty + 255) / 256) * (cy + 2 * T + 2);
-    if (cost < best) {
-      best = cost;
-      a.CY = cy;
-      a.nty = nty;
-    }
-  }
-  const int64_t tiles = cols * a.nty;
+  a.ntz = sp.ntz;
+  a.ntl = sp.ntl;
+  a.nty = sp.nty;
+  a.CY = sp.CY;
+  const int64_t tiles = sp.cols * sp.nty;
   if (tiles > (int64_t)1 << 30) return hipErrorInvalidConfiguration;
   a.ntiles = (int)tiles;
   a.tau = tau;
@@ -1017,9 +1081,9 @@ static hipError_t tv3d_pass(const ProxGeom& g, int T, const float2* v, float2* c
 // made of the scratch (work: four images, z and img_scratch: one each, z being
 // written only after the steps; and scratch, three, which may be p_in: it is
 // read by the first pass only, which does not write scratch).
-static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, const float2* v, float2* z,
-                             const float2* p_in, float2* p_out, const Dual3& scratch, float tau, float bound,
-                             float2* work, float2* img_scratch, hipStream_t s) {
+static hipError_t tv3d_steps(const ProxGeom& g, const Tv3dSplit* split, int n_inner, const float* mom,
+                             const float2* v, float2* z, const float2* p_in, float2* p_out, const Dual3& scratch,
+                             float tau, float bound, float2* work, float2* img_scratch, hipStream_t s) {
   const int64_t n = (int64_t)g.B * g.Ny * g.Nx * g.Nz;
   auto packed = [&](const float2* p) {
     float2* q = const_cast<float2*>(p);
@@ -1027,11 +1091,11 @@ static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, c
   };
   const Dual3 in = packed(p_in), out = packed(p_out), s1 = packed(work), s2{{work + 3 * n, z, img_scratch}},
               none = packed(nullptr);
-  const int passes = (n_inner + TV3_MAX_T - 1) / TV3_MAX_T;   // of at most TV3_MAX_T steps, as even as possible
+  const int passes = tv3d_passes(n_inner);
   Dual3 last = in, prev = none;
   int k = 0;
   for (int i = 0; i < passes; ++i) {
-    const int T = (n_inner - k + (passes - i) - 1) / (passes - i);
+    const int T = tv3d_pass_steps(n_inner - k, passes - i);
     const int left = passes - 1 - i;
     // where this pass leaves its last two duals: the pair with p_out when an even
     // number of passes is left (nothing follows the last one); scratch is in the
@@ -1039,7 +1103,8 @@ static hipError_t tv3d_steps(const ProxGeom& g, int n_inner, const float* mom, c
     const bool outer = left % 2 == 0, scratch_with_out = passes % 2 == 0;
     const Dual3 o = outer ? out : s2;
     const Dual3 op = left == 0 ? none : outer == scratch_with_out ? scratch : s1;
-    const hipError_t e = tv3d_pass(g, T, v, last.c, prev.c, k > 0 ? mom[k - 1] : 0.f, mom + k, o.c, op.c, tau, bound, s);
+    const hipError_t e = tv3d_pass(g, split[T], T, v, last.c, prev.c, k > 0 ? mom[k - 1] : 0.f, mom + k, o.c, op.c,
+                                   tau, bound, s);
     if (e != hipSuccess) return e;
     prev = op;
     last = o;
@@ -1096,7 +1161,8 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
   // coordinates are taken modulo each axis length.
   const int64_t np = d.n * d.nd;
   const int gb = grid_for(d.n, 256);
-  if (g.lateral_dims == 1) {   // inner steps past the tile kernel's halo: two passes per step
+  Tv3dSplit split[TV3_MAX_T + 1] = {};
+  if (g.lateral_dims == 1 || !tv3d_walks(g, n_inner, split)) {   // two kernels per step (B-scans: past the tile kernel's halo)
     float2* dd = work;
     float2* r = work + d.n;
     if (p_in) {
@@ -1111,7 +1177,7 @@ hipError_t launch_prox_tv(const ProxGeom& g, int n_inner, const float* mom, cons
       hipLaunchKernelGGL(tv_step_kernel, dim3(gb), dim3(256), 0, s, d, dd, r, p_out, step, mom[k]);
     }
   } else {
-    const hipError_t e = tv3d_steps(g, n_inner, mom, v, z, p_in, p_out, scratch, tau, bound, work, img_scratch, s);
+    const hipError_t e = tv3d_steps(g, split, n_inner, mom, v, z, p_in, p_out, scratch, tau, bound, work, img_scratch, s);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(tv_div_kernel, dim3(gb), dim3(256), 0, s, d, v, p_out, tau, bound, z);

@@ -106,3 +106,26 @@ for n in (512, 1225, 1400, 2000):
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+def test_small_and_narrow_volumes_step_in_two_kernels(stub):
+    """3-D TV: the walk along y where a volume fills its tiles, two kernels per step where it is
+    small or a few rows wide; a few steps on a small one are one pass of the walk."""
+    out = run_child(stub, r"""
+def prox(nz, nx, ny, inner, batch=1):
+    p = plan(nz, nx, nz, n_y=ny, lateral_dims=2, batch=batch)
+    f = lib.oct_prox
+    D = ctypes.c_double
+    st, names = kernels(f, p, 1, D(0.1), D(1.0), inner, 1, D(0.0), BUF, P(8192), None, None)
+    assert st == 0
+    lib.oct_plan_destroy(p)
+    return sum("tv3d_march" in n for n in names), sum("tv_step" in n for n in names)
+for args, walks in [((128, 16, 16, 10), False), ((2048, 8, 8, 10), False), ((1024, 4, 100, 10), False), ((1024, 1, 256, 20), False),
+                    ((256, 40, 45, 10), True), ((512, 32, 32, 10), True), ((512, 64, 64, 20), True), ((1024, 96, 96, 10), True),
+                    ((128, 16, 16, 5), False), ((128, 16, 16, 3), True), ((1024, 96, 96, 1), True)]:
+    march, step = prox(*args)
+    n = args[3]
+    assert (march, step) == ((-(-n // 3), 0) if walks else (0, n)), (args, march, step)
+print("ok")
+""")
+    assert out.strip() == "ok"
