@@ -667,28 +667,38 @@ hipError_t col_launch_t(const ColArgs& a, const float2* X, float2* W, const Pair
   return hipGetLastError();
 }
 
-template <int MODE>
-hipError_t col_launch(const ColArgs& a, const float2* X, float2* W, const PairRes& r, float2* Xo, hipStream_t s) {
+template <int J, int MODE>
+hipError_t col_launch_j(const ColArgs& a, const float2* X, float2* W, const PairRes& r, float2* Xo, hipStream_t s) {
+  constexpr bool few_cells = J == 8 && MODE == COL_FWD;   // five cells' eight weights each spill 30 registers
   int spt = 0, mb = 0;
-  const int nt = col_threads(a, &spt, &mb);
+  const int nt = col_threads(a, few_cells, &spt, &mb);
   if (nt == 0) return hipErrorInvalidConfiguration;
-#define COL_T(J, CN, SPT, MB) col_launch_t<J, MODE, CN, SPT, MB>(a, X, W, r, Xo, nt, s)
-  if (a.J == 4) return COL_T(4, 0, 5, 2);
-  if (a.J == 8) return COL_T(8, 0, 5, 2);
+#define COL_T(CN, SPT, MB) col_launch_t<J, MODE, CN, SPT, MB>(a, X, W, r, Xo, nt, s)
   if (spt == 2) {
     switch (a.Nz) {
-      case 512: return COL_T(6, 512, 2, 1);
-      case 1024: return COL_T(6, 1024, 2, 1);
-      default: return COL_T(6, 0, 2, 1);
+      case 512: return COL_T(512, 2, 1);
+      case 1024: return COL_T(1024, 2, 1);
+      default: return COL_T(0, 2, 1);
     }
   }
   switch (nt <= 512 ? a.Nz : 0) {
-    case 512: return COL_T(6, 512, 5, 2);
-    case 1024: return COL_T(6, 1024, 5, 2);
-    case 2048: return COL_T(6, 2048, 5, 1);
-    default: return spt == 3 ? COL_T(6, 0, 3, 2) : COL_T(6, 0, 5, 2);
+    case 512: return COL_T(512, 5, 2);
+    case 1024: return COL_T(1024, 5, 2);
+    case 2048: return COL_T(2048, 5, 1);
+    default: break;
   }
+  if constexpr (few_cells) return COL_T(0, 3, 2);
+  else return spt == 3 ? COL_T(0, 3, 2) : COL_T(0, 5, 2);
 #undef COL_T
+}
+
+template <int MODE>
+hipError_t col_launch(const ColArgs& a, const float2* X, float2* W, const PairRes& r, float2* Xo, hipStream_t s) {
+  switch (a.J) {
+    case 4: return col_launch_j<4, MODE>(a, X, W, r, Xo, s);
+    case 6: return col_launch_j<6, MODE>(a, X, W, r, Xo, s);
+    default: return col_launch_j<8, MODE>(a, X, W, r, Xo, s);
+  }
 }
 
 }  // namespace
@@ -710,18 +720,22 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 }
 
 // Threads per pair, base cells per thread and butterflies per thread.  Five
-// cells share ten-cell windows between five samples; with two butterflies per
-// thread the stages that run in place take no more threads than the cells do,
-// and more pairs share a CU.  Launches of at most eight waves a CU, where a
-// pair's chain is what counts, take two cells and one butterfly (forward of
-// 245 x 600, 301 pairs: 22.2 us a call against 24.4).
+// cells share ten-cell windows between five samples (J = 6); with two butterflies
+// per thread the stages that run in place take no more threads than the cells do,
+// and more pairs share a CU (2048: one, whose 512 threads the cells take anyway).
+// Launches of at most eight waves a CU, where a pair's chain is what counts, take
+// two cells and one butterfly (forward of 245 x 600, 301 pairs: 22.2 us a call
+// against 24.4).
 //
 // A CU holds 16 waves of these kernels, and a workgroup's waves go to its four
 // SIMDs in turn, so one of five waves takes the room of eight (1400 x 1120: 561
 // pairs in two rounds of 512).  Where three cells per thread fill more of it
 // than five they are taken (with the natural layout, both directions of 1400 x
-// 1120 50 -> 33 us).
-int col_threads(const ColArgs& a, int* spt, int* mb) {
+// 1120 50 -> 40 us).  The compiled lengths have the five-cell variant only.
+// few_cells: three rather than five in any case (the forward of J = 8: 128 x 512 x
+// 4 items 21.7 -> 19.5 us, 1920 x 400 37.0 -> 31.8; the adjoint's registers suffice
+// and five are better, 1600 x 1024 x 4 items 108 us against 129).
+int col_threads(const ColArgs& a, bool few_cells, int* spt, int* mb) {
   int items = 0;
   for (int s = 1; s < a.f.ns; ++s) items = std::max(items, 4 * (a.Nz / a.f.radix[s]));
   const int64_t pairs = (int64_t)a.n_pairs * a.batch;
@@ -731,13 +745,15 @@ int col_threads(const ColArgs& a, int* spt, int* mb) {
   *mb = 1;
   *spt = 2;
   int nt = threads(2, 1);
-  if (a.J == 6 && nt <= 1024 && pairs * (nt / 64) <= 8 * 256) return nt;
+  if (nt <= 1024 && pairs * (nt / 64) <= 8 * 256) return nt;
   *mb = a.Nz == 2048 ? 1 : 2;
   *spt = 5;
   nt = threads(5, *mb);
-  if (a.J == 6 && a.Nz != 512 && a.Nz != 1024 && a.Nz != 2048) {
+  const bool compiled = a.Nz == 512 || a.Nz == 1024 || a.Nz == 2048;
+  if (!compiled || (few_cells && nt > 512)) {
     auto resident = [](int t) { return t > 1024 ? 0 : 16 / ((t / 64 + 3) & ~3) * (t / 64); };
-    if (resident(threads(3, 2)) > resident(nt)) {
+    if (few_cells || resident(threads(3, 2)) > resident(nt)) {
+      *mb = 2;
       *spt = 3;
       nt = threads(3, 2);
     }
@@ -771,7 +787,7 @@ static bool col_cells_distinct(const ColArgs& a) {
 bool col_supported(const ColArgs& a) {
   int spt = 0, mb = 0;
   return a.f.ns > 0 && col_cells_distinct(a) &&
-         a.span + a.J - 1 <= 2 * a.Nz && col_lds_bytes(a.Nz) <= 150 * 1024 && col_threads(a, &spt, &mb) > 0;
+         a.span + a.J - 1 <= 2 * a.Nz && col_lds_bytes(a.Nz) <= 150 * 1024 && col_threads(a, a.J == 8, &spt, &mb) > 0;
 }
 
 hipError_t launch_col_fwd(const ColArgs& a, const float2* X1, float2* Wh, hipStream_t s) {

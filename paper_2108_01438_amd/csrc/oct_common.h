@@ -233,7 +233,7 @@ bool nufft_pair_supported(const NufftArgs& a);   // LDS and thread limits of the
 // both around the residual spectrum of a fully observed plan.
 bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw);
 bool col_supported(const ColArgs& a);
-int col_threads(const ColArgs& a, int* spt, int* mb);
+int col_threads(const ColArgs& a, bool few_cells, int* spt, int* mb);
 int col_row_cells(int N);
 size_t col_lds_bytes(int N);
 hipError_t launch_col_fwd(const ColArgs& a, const float2* X1, float2* Wh, hipStream_t s);
