@@ -163,8 +163,12 @@ def footprint_bytes(geom: Geometry, penalty: int = PEN_L1) -> int:
 
 def _stream_ptr(stream=None) -> int:
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the current stream's handle without a Stream object around it: 0.3 us in place of 2.9, of
+    # the 17.2 us that a call of three small kernels takes on the host (512 x 64 forward, a call
+    # among others: 17.1 -> 15.8 us)
+    return int(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev(t, dtype, shape, name):
