@@ -476,7 +476,8 @@ __global__ void __launch_bounds__(CN && SPT != 2 ? 512 : 1024, 4) column_pair_ke
 #pragma unroll
       for (int i = 0; i < SPT; ++i) {
         constexpr double two_pi = 6.283185307179586, inv_two_pi = 0.15915494309189535;
-        const double phase = coord((double)m[i]) * ict * a.df;
+        // t of the cell's sample; what an empty cell looked at may be evanescent and give no finite phase
+        const double phase = (in[i] ? coord((double)m[i]) : 0.0) * ict * a.df;
         const float f = (float)fma(-rint(phase * inv_two_pi), two_pi, phase);
         float sn, cs;
         sincosf(f, &sn, &cs);
