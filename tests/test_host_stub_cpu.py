@@ -1,6 +1,6 @@
 """The library's host code on the CPU: liboct on a HIP runtime without a device
 (tests/sanitize/hip_stub.c), whose launches leave the kernels' names.  Which
-kernels a plan's calls take."""
+kernels a plan's calls take, and every entry point under the host sanitizers."""
 import os
 import subprocess
 import sys
@@ -10,6 +10,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 STUB = os.path.join(HERE, "sanitize", "hip_stub.c")
 LIB = os.path.join(os.path.dirname(HERE), "paper_2108_01438_amd", "liboct.so")
+DRIVER = os.path.join(HERE, "sanitize", "host_sanitize_driver")
 
 
 @pytest.fixture(scope="module")
@@ -129,3 +130,19 @@ for args, walks in [((128, 16, 16, 10), False), ((2048, 8, 8, 10), False), ((102
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+# checks of values that kernels compute, which do nothing here
+VALUES = {"lipschitz positive", "ncc", "nothing observed: the solution is exactly zero"}
+
+
+def test_every_entry_point_under_host_sanitizers(stub):
+    """tests/sanitize/host_sanitize_driver.cpp with AddressSanitizer, UndefinedBehaviorSanitizer and
+    the leak check on the library's host code: no report, and every status as declared."""
+    assert os.path.exists(DRIVER), f"{DRIVER} is missing: run __graft_entry__.build()"
+    env = dict(os.environ, LD_LIBRARY_PATH=os.path.dirname(stub), ASAN_OPTIONS="halt_on_error=1:detect_leaks=1:exitcode=99",
+               LSAN_OPTIONS="exitcode=98", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
+    r = subprocess.run([DRIVER], capture_output=True, text=True, timeout=120, env=env)
+    bad = {l.split(": ", 1)[1].split(" (last error")[0] for l in r.stderr.splitlines() if l.startswith("UNEXPECTED")}
+    assert r.returncode in (0, 1) and "335 checks" in r.stderr, (r.returncode, r.stderr[-3000:])
+    assert bad <= VALUES, bad
