@@ -7,10 +7,11 @@
 // * Grid transforms.  The even cells of the K-point transform of a zero-padded
 //   column x are the N-point DFT of x, the odd cells the N-point DFT of
 //   x e^{-i pi n'/N} (n' = n - n_c): four N-point rows per pair instead of two
-//   K-point ones, with no zeros to transform, for any N.  Radices up to 16
-//   leave two or three stages (two LDS exchanges at 2048, where radix 8 on
-//   4096 points took three).  The first forward stage reads the column from
-//   memory once for both rows, the last inverse stage joins them into it.
+//   K-point ones, with no zeros to transform, for every N that col_plan can
+//   split.  Radices up to 16 leave two or three stages (two LDS exchanges at
+//   2048, where radix 8 on 4096 points took three).  The first forward stage
+//   reads the column from memory once for both rows, the last inverse stage
+//   joins them into it.
 // * Samples by grid cell.  Consecutive samples are at least one cell apart
 //   (t' >= K dz dk / pi), and the host takes these kernels where a cell is the
 //   base cell of at most one sample.  A thread owns SPT consecutive base cells, finds the
@@ -20,12 +21,15 @@
 //   thread adds its samples up in registers, passes what falls beyond its own
 //   cells to the next lanes, and writes every cell once.
 //
-// Bound by vector arithmetic: 17.7 k vector instructions per pair of 2048-point
-// columns at 0.77 of the issue rate (23.2 k at 0.69 in the pair kernel).  Both
-// directions in one launch, pair kernel -> here: 2048 x 256 x 256 1.90 -> 1.31
-// ms, 32 x 1024 x 512 311 -> 167 us, 1400 x 1120 74 -> 33 us, 512 x 64 15.2 ->
-// 9.5 us; the adjoint of 1024 x 112 x 112 145 -> 69 us, forward and adjoint of
-// 2048 x 1000 17.2 and 21.5 -> 16.5 and 15.8 us.
+// Bound by vector arithmetic on large launches of the compiled lengths: 17.6 k
+// vector instructions per pair of 2048-point columns, 0.78 of the issue rate
+// (23.2 k at 0.69 in the pair kernel).  At run-time lengths the stage switch, LDS
+// and barriers leave 0.37 of it (1400 x 1120: 561 pairs on 512 resident
+// workgroups, a second round of 49), and a few pairs are one pair's chain of
+// barriers.  Both directions in one launch, pair kernel -> here: 2048 x 256 x 256
+// 1.90 -> 1.30 ms, 32 x 1024 x 512 311 -> 167 us, 1400 x 1120 79 -> 39 us, 512 x
+// 64 15.2 -> 9.2 us; the adjoint of 1024 x 112 x 112 145 -> 69 us, forward and
+// adjoint of 2048 x 1000 17.2 and 21.5 -> 16.5 and 15.3 us.
 #include "oct_fft.h"
 
 #include <algorithm>
@@ -609,7 +613,8 @@ __global__ void __launch_bounds__(CN && SPT != 2 ? 512 : 1024, 4) column_pair_ke
 }
 
 // ns radices in increasing order: the first stage holds two rows per thread
-// (radix <= 12), the others run in place with one butterfly per thread; the
+// (radix <= 12), the others run in place with at most a butterfly for each of
+// 1024 threads (no plan: 1750, 1875, 2000, a few more, most above 2048); the
 // largest first radix wins (fewest butterflies)
 bool plan_radices(int N, int ns, int* best) {
   constexpr int set[] = {4, 5, 6, 7, 8, 9, 10, 12, 14, 15, 16};
@@ -732,7 +737,7 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 // SIMDs in turn, so one of five waves takes the room of eight (1400 x 1120: 561
 // pairs in two rounds of 512).  Where three cells per thread fill more of it
 // than five they are taken (with the natural layout, both directions of 1400 x
-// 1120 50 -> 40 us).  The compiled lengths have the five-cell variant only.
+// 1120 50 -> 39 us).  The compiled lengths have the five-cell variant only.
 // few_cells: three rather than five in any case (the forward of J = 8: 128 x 512 x
 // 4 items 21.7 -> 19.5 us, 1920 x 400 37.0 -> 31.8; the adjoint's registers suffice
 // and five are better, 1600 x 1024 x 4 items 108 us against 129).

@@ -839,7 +839,7 @@ __global__ void __launch_bounds__(256) sfb3_window(Dt3Geom g, DtJobs8 J) {
 }
 
 // y analysis of all eight trees in one thread with the level's detail bands
-// combined and shrunk (or summed) on the spot, as afb_lateral4_kernel.
+// combined and shrunk (or summed) on the spot, as in dt_analysis_kernel.
 template <bool SHRINK>
 __global__ void afb3_y8_kernel(Dt3Geom g, DtJobs8 J, float tau2, double* partial) {
   __shared__ double sh[16];

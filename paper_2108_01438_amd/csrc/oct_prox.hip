@@ -658,8 +658,9 @@ __global__ void tv_value_kernel(TvIdx d, const float2* __restrict__ z, double* p
 // spend more on halos (core 43 x 51 of 64 x 72 at ten steps, 43 x 107 of 64 x
 // 128); strips of nine are the longest that gain (ten: 58.6 us, eight: 62.1).
 // Two steps per turn of the loop spare the copies that swap the registers of r
-// and P, and 1.9 us, but spill to scratch memory: not used.  Ten steps on
-// 2048 x 1000: 62.8 -> 54.9 us; on 8 x 1024 x 512: 131 -> 115 us.
+// and P (53.0 us on 2048 x 1000), but spill 8 to 64 bytes per lane ahead of it:
+// not used.  Ten steps on 2048 x 1000: 62.8 -> 54.9 us; on 8 x 1024 x 512: 131 ->
+// 115 us.
 // ---------------------------------------------------------------------------
 constexpr int TV_S1 = 9, TV_W1 = 8;
 constexpr int TV_S2 = 8, TV_W2 = 16;
