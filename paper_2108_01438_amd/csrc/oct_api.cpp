@@ -151,7 +151,7 @@ bool factorize(int n, FftDesc& d) {
 // radix-8 plan d: 26.0 -> 19.2 us for the forward pass of 1400 x 1120, 544 ->
 // 513 us a pass of the 2048 x 256 x 256 volume; with as many, its one
 // butterfly per thread costs resident tiles (26.4 -> 28.8 us for the seam of
-// 8 x 1024 x 512).
+// 8 x 1024 x 512).  lateral_wide says which line sets gain.
 bool factorize_wide(const FftDesc& d, FftDesc& w) {
   const CtPlan c = ct_wide(d.n);
   std::memset(&w, 0, sizeof(w));
@@ -960,8 +960,8 @@ oct_status oct_plan_create(const oct_geometry* g, const uint8_t* mask, oct_plan_
   {
     FftDesc w;
     const int rows = (int)std::min(p->Nz, p->Mk);
-    if (factorize_wide(p->fX, w) && lateral_wide(lines_x(p, rows), w)) p->fX = w;
-    if (factorize_wide(p->fY, w) && lateral_wide(lines_y(p, rows), w)) p->fY = w;
+    if (factorize_wide(p->fX, w) && lateral_wide(lines_x(p, rows), p->fX, w)) p->fX = w;
+    if (factorize_wide(p->fY, w) && lateral_wide(lines_y(p, rows), p->fY, w)) p->fY = w;
   }
 
   oct_status st = OCT_OK;

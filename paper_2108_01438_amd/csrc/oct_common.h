@@ -205,7 +205,7 @@ struct ColArgs {
 // Launchers (kernels in the .hip files; all asynchronous on `s`).
 hipError_t launch_lateral(LatMode mode, const LatArgs& a, hipStream_t s);
 int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride);
-bool lateral_wide(const LineGeom& lg, const FftDesc& fd);
+bool lateral_wide(const LineGeom& lg, const FftDesc& d, const FftDesc& w);
 hipError_t launch_nufft_fwd(const NufftArgs& a, const float2* X1, float2* W, hipStream_t s);
 hipError_t launch_nufft_adj(const NufftArgs& a, const float2* Rh, float2* X, hipStream_t s);
 size_t nufft_adj_lds_bytes(const NufftArgs& a);

@@ -528,18 +528,36 @@ int lateral_pick_tile(const LineGeom& lg, const FftDesc& fd, int* rowstride) {
   return 0;
 }
 
-// Whether a line set takes the wide plan fd: if the widest tile still has a
-// thread for every butterfly (the radix-8 plan runs two per thread instead of
-// narrowing the tile), and its own tile has butterflies for three waves (with
-// fewer, as on small images, the long butterflies of one or two waves are the
-// pass: forward of 1750 x 128, 64 butterflies of radix 8 and 16, 24.5 us a
-// call against 23.8).
-bool lateral_wide(const LineGeom& lg, const FftDesc& fd) {
-  const int rs0 = (lg.L % 2 == 0) ? lg.L + 1 : lg.L;
-  int T = 32, rs = 0;
-  while (T > 1 && (int64_t)T * rs0 * 8 > 65280) T >>= 1;
-  if ((int64_t)T * (lg.L / fd.min_radix) > 1024) return false;
-  return (int64_t)lateral_pick_tile(lg, fd, &rs) * (lg.L / fd.min_radix) >= 192;
+// Whether a line set takes the wide plan w instead of its radix-8 plan d (w has
+// fewer stages).  Not
+// * if the widest tile has no thread for every butterfly (the radix-8 plan runs
+//   two per thread instead of narrowing the tile);
+// * if its own tile has butterflies for fewer than three waves, as on small
+//   images: the long butterflies of one or two waves are then the pass (forward
+//   of 1750 x 128, 64 butterflies of radix 8 and 16, 24.5 us a call against 23.8);
+// * where it widens a one-row tile to two and the launch has few of them (fewer
+//   workgroups are left; 20 l1 iterations on 80 x 3840 294 us against 332), while
+//   from 128 on it gains (1800 x 2058 1.40 times);
+// * for one stage less on two-row tiles, which then hold 10 to 13 waves in place
+//   of 8 to a workgroup and fewer workgroups to a CU (360 x 2560 x 5 items 1004 us
+//   against 1193, 1225 x 3136 1080 against 1210);
+// * for one stage less at a run-time length on a launch that leaves CUs idle,
+//   where the stage's switch costs what the stage gains (24 x 1120 0.94, 98 x 1280
+//   0.95; from 256 tiles on 1.03 on average).
+// Two stages less or more gain up to 40% elsewhere (0.97 at the least).
+bool lateral_wide(const LineGeom& lg, const FftDesc& d, const FftDesc& w) {
+  const int rs0 = (lg.L % 2 == 0) ? lg.L + 1 : lg.L, bf = lg.L / w.min_radix;
+  int T0 = 32, rs = 0;
+  while (T0 > 1 && (int64_t)T0 * rs0 * 8 > 65280) T0 >>= 1;
+  if ((int64_t)T0 * bf > 1024) return false;
+  const int T = lateral_pick_tile(lg, w, &rs);
+  if ((int64_t)T * bf < 192) return false;
+  const int64_t tiles = (int64_t)lg.n_lines * ((lg.rows + T - 1) / T);
+  if (T > lateral_pick_tile(lg, d, &rs)) return tiles >= 128;
+  if (d.nstages - w.nstages > 1) return true;
+  bool compiled = false;
+  for (int n : {OCT_CT_LAT_WIDE}) compiled = compiled || n == lg.L;
+  return T0 != 2 && (compiled || tiles >= 256);
 }
 
 template <int MODE, int VAR, bool OFF32>
