@@ -932,6 +932,28 @@ struct Tv2dTiles {
   int waves, CZ, CL, ntz, ntl;
 };
 
+// Times (us) of tiles and n inner steps from a warm dual, by rounds of workgroups
+// over the 256 CUs: two of the 64 x 72 tiles share a CU (one loads and stores
+// while the other computes), one of the 64 x 128 fills it.  Past the first round
+// the next workgroups overlap the last ones'.  Fitted to 11984 sizes and step
+// counts; the choice costs 0.2 % on average against the better tile of each (a
+// rule on the loaded samples, 3.4 %).  Measured, small against large (us): 2048 x
+// 1000 with 10 steps 54.9 / 62.8, 16 steps 138 / 124, 20 steps 259 / 222; 8 x 1024
+// x 512 with 10 steps 115 / 131; 512 x 64 with 10 steps 19.5 / 25.9; where the
+// small tiles just miss a round (546 and 528 on 512 places) 1458 x 540 with 14
+// steps 61 / 46, 600 x 1890 with 10 steps 40 / 29.
+static double tv2d_us_small(int64_t tiles, int n) {
+  const double one = 7.8 + 1.15 * n, two = 5.8 + 2.28 * n;   // a round of one and of two workgroups per CU
+  if (tiles <= 256) return one;
+  if (tiles <= 512) return two;
+  return std::max(two + 0.62 * one, 0.8 * (double)tiles / 512.0 * two + 0.44 * one);
+}
+
+static double tv2d_us_large(int64_t tiles, int n) {
+  const double one = 9.7 + 1.91 * n;
+  return tiles <= 256 ? one : std::max(1.86 * one, 0.94 * (double)tiles / 256.0 * one + 0.2 * one);
+}
+
 static Tv2dTiles tv2d_tiles(const ProxGeom& g, int n_inner, bool value) {
   const int halo = 2 * n_inner + (value ? 2 : 1);
   auto make = [&](int strip, int waves) {
@@ -944,14 +966,8 @@ static Tv2dTiles tv2d_tiles(const ProxGeom& g, int n_inner, bool value) {
     return t;
   };
   const Tv2dTiles t1 = make(TV_S1, TV_W1), t2 = make(TV_S2, TV_W2);
-  // Loaded samples of the 64 x 72 tiles against those of the 64 x 128 ones, a
-  // sample of the small tiles costing about 0.8 (two workgroups per CU: one
-  // loads and stores while the other computes).  Measured, small against large
-  // (us): 2048 x 1000 with 10 steps 54.9 / 62.8, 13 steps 103 / 106, 16 steps
-  // 138 / 124, 20 steps 259 / 222; 8 x 1024 x 512 with 10 steps 115 / 131, 16
-  // steps 257 / 263; 512 x 64 with 10 steps 19.5 / 25.9.
-  const int64_t n1 = (int64_t)t1.ntz * t1.ntl * TV_S1 * TV_W1, n2 = (int64_t)t2.ntz * t2.ntl * TV_S2 * TV_W2;
-  return n1 * 4 <= n2 * 5 ? t1 : t2;
+  const int64_t n1 = (int64_t)t1.ntz * t1.ntl * g.B, n2 = (int64_t)t2.ntz * t2.ntl * g.B;
+  return 1.02 * tv2d_us_small(n1, n_inner) <= tv2d_us_large(n2, n_inner) ? t1 : t2;
 }
 
 template <int ST, int WAVES>

@@ -146,3 +146,18 @@ def test_every_entry_point_under_host_sanitizers(stub):
     bad = {l.split(": ", 1)[1].split(" (last error")[0] for l in r.stderr.splitlines() if l.startswith("UNEXPECTED")}
     assert r.returncode in (0, 1) and "335 checks" in r.stderr, (r.returncode, r.stderr[-3000:])
     assert bad <= VALUES, bad
+
+
+def test_bscan_tv_tiles_by_rounds(stub):
+    """64 x 72 tiles, two to a CU, but where they just miss a round that the 64 x 128 ones keep."""
+    out = run_child(stub, r"""
+D = ctypes.c_double
+for nz, nx, batch, inner, waves in [(2048, 1000, 1, 10, 8), (1024, 512, 8, 10, 8), (512, 64, 1, 10, 8), (2048, 1000, 1, 16, 16),
+                                    (600, 1890, 1, 10, 16), (1280, 384, 1, 18, 16), (45, 540, 14, 10, 16), (36, 252, 14, 22, 16)]:
+    p = plan(nz, nx, nz, batch=batch)
+    st, names = kernels(lib.oct_prox, p, 1, D(0.1), D(1.0), inner, 1, D(0.0), BUF, P(8192), None, None)
+    assert st == 0 and len(names) == 1 and f"Li{waves}E" in names[0], (nz, nx, inner, names)
+    lib.oct_plan_destroy(p)
+print("ok")
+""")
+    assert out.strip() == "ok"
