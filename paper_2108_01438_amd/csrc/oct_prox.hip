@@ -1020,30 +1020,33 @@ static int tv3d_pass_steps(int left, int passes_left) {   // as even as possible
 
 // Whether a volume takes the walk along y (its passes by steps in split, zero on
 // entry) or two kernels per step (d = v + tau div r stored, then r and p).  A
-// pass of the walk is a chain of planes (1.9, 3.1 and 4.9 us each with 1, 2 and 3
-// steps; 1.9, 2.4 and 3.7 in the first pass, which reads one dual), three and
-// more of them halo, however small the volume.  The two kernels take 5 to 7 us a
-// step, as fast as the host launches them, until the memory traffic shows (24 us
-// per million samples), and copy the dual once.  So small volumes, and those a
-// few rows wide (an empty tile costs as much), keep the two kernels for more than
-// a few steps.  Measured, walk against two kernels, 10 steps (us): 128 x 16 x 16
-// 103 / 88, 2048 x 8 x 8 125 / 87, 1024 x 4 x 100 208 / 148, 1024 x 1 x 256
-// 359 / 120, 512 x 20 x 20 120 / 104; 256 x 40 x 45 137 / 149, 512 x 32 x 32
-// 146 / 168, 512 x 64 x 64 274 / 556; three steps on 128 x 16 x 16 31 / 28 to 37.
+// pass of the walk is a chain of planes (2.0, 3.5 and 4.7 us each with 1, 2 and 3
+// steps; 1.9, 2.7 and 3.8 in the first pass, which reads one dual), three and
+// more of them halo, however small the volume.  The two kernels take about 6.5 us
+// a step, as fast as the host launches them, until the memory traffic shows (23
+// us per million samples), and copy the dual first.  So small volumes, and those
+// a few rows wide (an empty tile costs as much), keep the two kernels for more
+// than two steps.  Fitted to 1425 volumes with 2 to 20 steps; the choice costs
+// 0.1 % on average against the better way of each and more than 4 % against the
+// two kernels in 49 of 8550.  Measured, walk against two kernels, 10 steps (us):
+// 128 x 16 x 16 103 / 88, 2048 x 8 x 8 125 / 87, 1024 x 4 x 100 208 / 148, 1024 x
+// 1 x 256 359 / 120, 512 x 20 x 20 120 / 104; 256 x 40 x 45 137 / 149, 512 x 32 x
+// 32 146 / 168, 512 x 64 x 64 274 / 556; three steps on 128 x 16 x 16 31 / 28 to
+// 37.
 static bool tv3d_walks(const ProxGeom& g, int n_inner, Tv3dSplit* split) {
-  static const double first_us[TV3_MAX_T + 1] = {0, 1.9, 2.4, 3.7}, plane_us[TV3_MAX_T + 1] = {0, 1.9, 3.1, 4.9};
+  static const double first_us[TV3_MAX_T + 1] = {0, 1.9, 2.7, 3.8}, plane_us[TV3_MAX_T + 1] = {0, 2.0, 3.5, 4.7};
   const double mpx = 1e-6 * (double)g.B * g.Ny * g.Nx * g.Nz;
-  const double two = std::max(10.5, 13.3 * mpx) + n_inner * std::max(6.5, 3.5 + 24.0 * mpx);
+  const double two = std::max(4.7, 20.0 * mpx) + n_inner * std::max(6.5, 6.0 + 23.4 * mpx);
   double walk = 0.0;
   const int passes = tv3d_passes(n_inner);
   for (int i = 0, k = 0; i < passes; ++i) {
     const int T = tv3d_pass_steps(n_inner - k, passes - i);
     Tv3dSplit& s = split[T];
     if (s.rounds == 0) s = tv3d_split(g, T);
-    walk += 2.5 + (double)s.rounds * (s.CY + 2 * T) * (i == 0 ? first_us : plane_us)[T];
+    walk += 2.0 + (double)s.rounds * (s.CY + 2 * T) * (i == 0 ? first_us : plane_us)[T];
     k += T;
   }
-  return 1.05 * walk < two;
+  return 1.03 * walk < two;
 }
 
 static hipError_t tv3d_pass(const ProxGeom& g, const Tv3dSplit& sp, int T, const float2* v, float2* const* p,

@@ -123,7 +123,7 @@ def prox(nz, nx, ny, inner, batch=1):
     return sum("tv3d_march" in n for n in names), sum("tv_step" in n for n in names)
 for args, walks in [((128, 16, 16, 10), False), ((2048, 8, 8, 10), False), ((1024, 4, 100, 10), False), ((1024, 1, 256, 20), False),
                     ((256, 40, 45, 10), True), ((512, 32, 32, 10), True), ((512, 64, 64, 20), True), ((1024, 96, 96, 10), True),
-                    ((128, 16, 16, 5), False), ((128, 16, 16, 3), True), ((1024, 96, 96, 1), True)]:
+                    ((128, 16, 16, 3), False), ((128, 16, 16, 2), True), ((1024, 96, 96, 1), True)]:
     march, step = prox(*args)
     n = args[3]
     assert (march, step) == ((-(-n // 3), 0) if walks else (0, n)), (args, march, step)
