@@ -21,10 +21,10 @@
 //   thread adds its samples up in registers, passes what falls beyond its own
 //   cells to the next lanes, and writes every cell once.
 //
-// Bound by vector arithmetic on large launches of the compiled lengths: 17.6 k
+// Bound by vector arithmetic on large launches of the compiled lengths: 17.7 k
 // vector instructions per pair of 2048-point columns, 0.78 of the issue rate
 // (23.2 k at 0.69 in the pair kernel).  At run-time lengths the stage switch, LDS
-// and barriers leave 0.37 of it (1400 x 1120: 561 pairs on 512 resident
+// and barriers leave 0.32 of it (1400 x 1120: 561 pairs on 512 resident
 // workgroups, a second round of 49), and a few pairs are one pair's chain of
 // barriers.  Both directions in one launch, pair kernel -> here: 2048 x 256 x 256
 // 1.90 -> 1.30 ms, 32 x 1024 x 512 311 -> 167 us, 1400 x 1120 79 -> 39 us, 512 x
@@ -737,7 +737,9 @@ bool col_plan(int N, ColPlan* f, ColPlan* i, std::vector<float2>* tw) {
 // SIMDs in turn, so one of five waves takes the room of eight (1400 x 1120: 561
 // pairs in two rounds of 512).  Where three cells per thread fill more of it
 // than five they are taken (with the natural layout, both directions of 1400 x
-// 1120 50 -> 39 us).  The compiled lengths have the five-cell variant only.
+// 1120 50 -> 39 us), and where every pair has a CU to itself, for the shorter
+// chain (2240 x 36: both directions 22.8 -> 19.3 us, forward 11.9 -> 11.4).  The
+// compiled lengths have the five-cell variant only.
 // few_cells: three rather than five in any case (the forward of J = 8: 128 x 512 x
 // 4 items 21.7 -> 19.5 us, 1920 x 400 37.0 -> 31.8; the adjoint's registers suffice
 // and five are better, 1600 x 1024 x 4 items 108 us against 129).
@@ -758,7 +760,7 @@ int col_threads(const ColArgs& a, bool few_cells, int* spt, int* mb) {
   const bool compiled = a.Nz == 512 || a.Nz == 1024 || a.Nz == 2048;
   if (!compiled || (few_cells && nt > 512)) {
     auto resident = [](int t) { return t > 1024 ? 0 : 16 / ((t / 64 + 3) & ~3) * (t / 64); };
-    if (few_cells || resident(threads(3, 2)) > resident(nt)) {
+    if (few_cells || (pairs <= 256 && threads(3, 2) <= 1024) || resident(threads(3, 2)) > resident(nt)) {
       *mb = 2;
       *spt = 3;
       nt = threads(3, 2);
